@@ -170,7 +170,7 @@ struct gmg_plan {
   // per level and role (0: descent / pre-smoothing, 1: ascent / post-smoothing
   // with the fused prolongation): sweeps per pass and the tile shape and
   // z-chunk for each stage count
-  std::vector<std::array<PassChoice, 3>> ch;  // role 2: the cross-cycle pass (level 0)
+  std::vector<std::array<PassChoice, 3>> ch;  // role 2: the three-stage level-0 pass (cross, carry)
   // FP64 red-black V(1,1) with Algorithm 1's backward post-smoothing: the
   // solve loop runs the cross-cycle schedule (one level-0 pass per cycle that
   // ends the cycle's post-smoothing and starts the next cycle's
@@ -179,6 +179,10 @@ struct gmg_plan {
   // mixed V(1,1) with the same sweep orders: the FP32 cycles of a refinement
   // step run that schedule among themselves
   bool cross32 = false;
+  // red-black V(nu1 >= 2, nu2) with the same sweep orders: a cycle that starts
+  // from the previous cycle's result leaves out its first red half-sweep
+  // (carry_pre)
+  bool carry = false;
 
   // profiling
   bool profile = false;
@@ -525,7 +529,17 @@ bool can_fuse_cross(const gmg_plan *p, size_t elem) {
   if (!c.fuse || (p->cfg.flags & GMG_NO_FUSED_RESTRICT)) return false;
   const PassTile t = pass_variant(p->dim, 3, 0, c.var[3]);
   if (pass_geometry(p->dim, p->m[0], 3, t, c.tz[3], true).nblocks > kMaxPartials) return false;
-  return rb_pass_fits(p->dim, 3, c.var[3], F_PROLONG | F_RESTRICT, elem);
+  return rb_pass_fits(p->dim, 3, c.var[3], (p->carry ? F_NORM_IN : F_PROLONG) | F_RESTRICT, elem);
+}
+
+// The tile of the three-stage pass for the form it runs next: a tile made for
+// the folded form (odd row count) cannot run the plain one, which then takes
+// the first tile of the table.  Returns the launch's workgroup count.
+int three_stage_tile(gmg_plan *p, int plain_flags, bool folded, size_t elem) {
+  PassChoice &c = p->ch[0][2];
+  if (!folded && !rb_pass_fits(p->dim, 3, c.var[3], plain_flags, elem)) c.var[3] = 0;
+  return pass_geometry(p->dim, p->m[0], 3, pass_variant(p->dim, 3, 0, c.var[3]), c.tz[3], folded)
+      .nblocks;
 }
 
 // partials != NULL (FP64 solves): the pass emits the norm of u_k's residual.
@@ -536,16 +550,43 @@ hipError_t cross_pass(gmg_plan *p, const T *w, const T *ec, const T *f, T *w_nex
                       double *partials, const int *active, T *fc, bool *fused, int *nparts) {
   const bool fz = can_fuse_cross(p, sizeof(T));
   *fused = fz;
-  PassChoice &c = p->ch[0][2];
-  // a tile made for the folded form (odd row count) cannot run the plain
-  // one: the plain form then takes the first tile of the table
-  if (!fz && !rb_pass_fits(p->dim, 3, c.var[3], F_PROLONG, sizeof(T))) c.var[3] = 0;
-  *nparts = pass_geometry(p->dim, p->m[0], 3, pass_variant(p->dim, 3, 0, c.var[3]), c.tz[3], fz)
-                .nblocks;
+  *nparts = three_stage_tile(p, F_PROLONG, fz, sizeof(T));
   const int flags =
       F_PROLONG | F_BLACK_FIRST | (partials ? F_NORM_MID : 0) | (fz ? F_RESTRICT : 0);
   return one_pass_st<T>(p, 0, 2, 3, flags, w, ec, f, w_next, partials, active, PC_CROSS0,
                         fz ? fc : nullptr);
+}
+
+// The level-0 pre-smoothing of a cycle that starts from the previous cycle's
+// result (red-black, Algorithm 1's orders: that cycle ended with a red
+// half-sweep over the same right-hand side).  The forward sweep's first red
+// half-sweep would recompute those red values from the same black values, so
+// it is left out: black, red, black for nu1 = 2, in one three-stage pass
+// instead of a four-stage one.  A shorter halo, and enough LDS and registers
+// left for the folded restriction: the four-stage pass spills with it, so the
+// restriction was a kernel of its own, another read of w and f.  HBM bound,
+// 25 B per point instead of 24 + 17.  511^3 FP64: 848-893 us against 723 +
+// 599 us (V(2,2) solve 30.1 -> 24.8 ms); 255^3: 127 against 93 + 60 us.
+// nu1 > 2: the remaining sweeps follow as a chain.  Same iterates, same norm
+// of u's residual (partials).  A batch keeps the four-stage pass: sharing its
+// launches among problems the two forms came out equal (35.9 ms both).
+template <typename T>
+hipError_t carry_pre(gmg_plan *p, const T *u, const T *f, T *w, T *tmp, double *partials,
+                     const int *active, T *fc, bool *fused, int *nparts) {
+  const int left = p->cfg.nu1 - 2;  // sweeps after the three stages
+  const bool fz = left == 0 && can_fuse_cross(p, sizeof(T));
+  const int nb = three_stage_tile(p, partials ? F_NORM_IN : 0, fz, sizeof(T));
+  if (nparts) *nparts = nb;
+  *fused = fz;
+  const int flags = F_BLACK_FIRST | (partials ? F_NORM_IN : 0) | (fz ? F_RESTRICT : 0);
+  // the chain's first pass writes w after an odd number of passes, else tmp
+  const int smax = p->ch[0][0].smax;
+  T *out = left > 0 && ((left + smax - 1) / smax) % 2 == 1 ? tmp : w;
+  hipError_t e = one_pass_st<T>(p, 0, 2, 3, flags, u, nullptr, f, out, partials, active, PC_PRE0,
+                                fz ? fc : nullptr);
+  if (e != hipSuccess || left == 0) return e;
+  return smooth_chain<T>(p, 0, left, false, out, nullptr, f, w, tmp, nullptr, active, PC_PRE0,
+                         nullptr, fc, fused);
 }
 
 // Level-0 buffers of the cross-cycle schedule: w_k (the pre-smoothed
@@ -680,9 +721,10 @@ hipError_t run_coarse(gmg_plan *p, const int *active) {
 // u0_in (NULL = zero), result u0_out (must not alias u0_in), RHS f0.
 // norm_partials != NULL: the level-0 pre-pass emits the residual norm of
 // u0_in, and a finalize step updates the solve state right after it.
+// repeat: u0_in is the result of this plan's previous cycle on f0.
 template <typename T>
 hipError_t enqueue_vcycle(gmg_plan *p, const T *u0_in, const T *f0, T *u0_out,
-                          double *norm_partials, const int *active) {
+                          double *norm_partials, const int *active, bool repeat = false) {
   LevelSet<T> &S = levels_of<T>(p);
   const int L = p->L;
   const bool bwd = !(p->cfg.flags & GMG_POST_FORWARD);
@@ -717,8 +759,13 @@ hipError_t enqueue_vcycle(gmg_plan *p, const T *u0_in, const T *f0, T *u0_out,
   }
   // ---- descent
   bool fused = false;
-  e = smooth_chain<T>(p, 0, nu1, false, u0_in, nullptr, f0, S.w[0], S.t[0], norm_partials, active,
-                      PC_PRE0, &nparts, S.f[1], &fused);
+  // (a descent of single-sweep passes stays one: its level is one where short
+  // passes are the faster ones)
+  if (repeat && p->carry && p->ch[0][0].smax >= 2)
+    e = carry_pre<T>(p, u0_in, f0, S.w[0], S.t[0], norm_partials, active, S.f[1], &fused, &nparts);
+  else
+    e = smooth_chain<T>(p, 0, nu1, false, u0_in, nullptr, f0, S.w[0], S.t[0], norm_partials,
+                        active, PC_PRE0, &nparts, S.f[1], &fused);
   if (e != hipSuccess) return e;
   // (nu1 == 0: the chain copied the start value into w0, so the post-pass
   // below never reads the array it writes)
@@ -783,7 +830,7 @@ hipError_t enqueue_inner(gmg_plan *p, const int *active) {
   if (!p->cross32) {
     for (int c = 0; c < K; ++c) {
       hipError_t e = enqueue_vcycle<float>(p, c == 0 ? nullptr : S.u[0], S.f[0], S.u[0], nullptr,
-                                           active);
+                                           active, c > 0);
       if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -1208,6 +1255,9 @@ gmg_status init_plan_shape(gmg_plan &p, const gmg_config *cfg) {
                         !(cfg->flags & (GMG_POST_FORWARD | GMG_NO_CROSS_CYCLE));
   p.cross = cross_ok && cfg->precision == GMG_FP64;
   p.cross32 = cross_ok && cfg->precision == GMG_MIXED_FP32_IR;
+  p.carry = cfg->smoother == GMG_SMOOTH_RBGS && !cfg_variant(p.cfg) && cfg->nu1 >= 2 &&
+            cfg->nu2 >= 1 && p.L >= 2 && p.smax_cap >= 2 &&
+            !(cfg->flags & (GMG_POST_FORWARD | GMG_NO_CROSS_CYCLE));
   p.profile = (cfg->flags & GMG_PROFILE) != 0;
   return GMG_OK;
 }
@@ -1276,7 +1326,7 @@ std::string tune_key(const gmg_plan &p, int l, int role, size_t elem) {
   char buf[192];
   std::snprintf(buf, sizeof(buf), "%s|d%d|m%d|f%d|%s|nu%d|r%d|cap%d|fr%d|z4|t%08x",
                 arch_name().c_str(), p.dim, p.m[l], (int)(elem * 8),
-                p.cfg.smoother == GMG_SMOOTH_WJ ? "wj" : "rbgs", role == 0 ? p.cfg.nu1 : p.cfg.nu2,
+                p.cfg.smoother == GMG_SMOOTH_WJ ? "wj" : "rbgs", role == 1 ? p.cfg.nu2 : p.cfg.nu1,
                 role, p.smax_cap, (p.cfg.flags & GMG_NO_FUSED_RESTRICT) ? 0 : 1,
                 (unsigned)tile_table_hash());
   return buf;
@@ -1510,7 +1560,8 @@ hipError_t tune_role(gmg_plan *p, int l, int role, const T *src, const T *ec, co
   return err;
 }
 
-// The cross-cycle pass (role 2 of level 0) is tuned like the other roles:
+// The three-stage pass (role 2 of level 0: the cross-cycle pass, or without
+// ec the pre-smoothing of a repeated cycle) is tuned like the other roles:
 // every three-stage tile and z-chunk, with the restriction folded in where
 // the tile allows it and as a kernel of its own, each timed together with
 // the step that follows it in the solve (the stop test as a kernel of its
@@ -1539,10 +1590,20 @@ hipError_t tune_cross(gmg_plan *p, const T *w, const T *ec, const T *f, T *wn, T
   const int reps = N > (1u << 24) ? 2 : (N > (1u << 20) ? 4 : 10);
   const PassChoice base = p->ch[0][2];
   // the pass and the step after it in the solve, with p->ch[0][2]
+  // (nu1 > 2: of a repeated cycle's pre-smoothing only the three-stage pass,
+  // whose fold and the sweeps after it are the descent's own choice)
+  const bool alone = !ec && p->cfg.nu1 > 2;
   auto run = [&]() -> hipError_t {
     bool fused = false;
     int nparts = 0;
-    hipError_t e2 = cross_pass<T>(p, w, ec, f, wn, parts, nullptr, fc, &fused, &nparts);
+    if (alone) {
+      three_stage_tile(p, parts ? F_NORM_IN : 0, false, sizeof(T));
+      return one_pass_st<T>(p, 0, 2, 3, F_BLACK_FIRST | (parts ? F_NORM_IN : 0), w, nullptr, f,
+                            wn, parts, nullptr, PC_MISC);
+    }
+    hipError_t e2 =
+        ec ? cross_pass<T>(p, w, ec, f, wn, parts, nullptr, fc, &fused, &nparts)
+           : carry_pre<T>(p, w, f, wn, nullptr, parts, nullptr, fc, &fused, &nparts);
     if (e2 != hipSuccess) return e2;
     if (fused) return parts ? launch_finalize(parts, nparts, p->state, p->stream) : hipSuccess;
     return restrict_level<T>(p, 0, wn, f, fc, nullptr, PC_MISC, parts, parts ? nparts : 0);
@@ -1560,8 +1621,8 @@ hipError_t tune_cross(gmg_plan *p, const T *w, const T *ec, const T *f, T *wn, T
         c.fuse = fz;
         p->ch[0][2] = c;
         // each tile runs one form or both (folded: odd row count)
-        if (fz ? !can_fuse_cross(p, sizeof(T))
-               : !rb_pass_fits(p->dim, 3, v, F_PROLONG, sizeof(T)))
+        if (fz ? alone || !can_fuse_cross(p, sizeof(T))
+               : !rb_pass_fits(p->dim, 3, v, ec ? F_PROLONG : parts ? F_NORM_IN : 0, sizeof(T)))
           continue;
         double us = 0.0;
         err = time_runs(p, e0, e1, reps, run, us);
@@ -1601,7 +1662,7 @@ hipError_t tune_plan(gmg_plan *p, const T *src0, const T *f0, double *partials0)
   p->profile = false;
   // the timed level-0 steps update the solve state like a solve does; give
   // it defined contents (the solve initialises it again afterwards)
-  hipError_t e = (partials0 || p->cross) ? launch_state_init(p->state, 1, 1.0, -1.0, p->stream)
+  hipError_t e = (partials0 || p->cross || (p->carry && sizeof(T) == 8)) ? launch_state_init(p->state, 1, 1.0, -1.0, p->stream)
                                          : hipSuccess;
   if (e != hipSuccess) {
     p->profile = prof;
@@ -1619,6 +1680,8 @@ hipError_t tune_plan(gmg_plan *p, const T *src0, const T *f0, double *partials0)
     e = tune_role<T>(p, l, 1, src, S.u[l + 1], f, dst, S.t[l], nullptr, sizeof(T));
     if (e == hipSuccess && l == 0 && (sizeof(T) == 8 ? p->cross : p->cross32))
       e = tune_cross<T>(p, S.w[0], S.u[1], f, S.t[0], S.f[1]);
+    if (e == hipSuccess && l == 0 && p->carry)
+      e = tune_cross<T>(p, S.w[0], nullptr, f, S.t[0], S.f[1]);
   }
   p->profile = prof;
   p->tuned = true;
@@ -2110,7 +2173,7 @@ gmg_status batch_setup(const gmg_config *cfg, int n, const int *dims, const int 
   }
   gmg_plan tmp;
   init_plan_shape(tmp, &c);
-  tmp.cross = false;
+  tmp.cross = tmp.carry = false;
   Batch tw;  // the most launches any tile choice can give sizes the table region
   tw.worst = true;
   batch_build(&tmp, &tw, n, dims, levels, nullptr);
@@ -2127,7 +2190,8 @@ gmg_status batch_setup(const gmg_config *cfg, int n, const int *dims, const int 
   if (((uintptr_t)workspace) % kAlign) return GMG_ERR_WORKSPACE;
   gmg_plan *p = new gmg_plan();
   init_plan_shape(*p, &c);
-  p->cross = false;  // batches run the two-pass schedule on every problem
+  // batches run the two-pass schedule with every half-sweep on every problem
+  p->cross = p->carry = false;
   p->nproblems = n;
   p->stream = (hipStream_t)stream;
   p->ws = (char *)workspace;
@@ -2177,7 +2241,7 @@ hipError_t batch_tune(gmg_plan *p, double *const *u, const double *const *f) {
     c.flags = c.flags & ~(unsigned)GMG_PROFILE;
     gmg_plan v;
     init_plan_shape(v, &c);
-    v.cross = false;
+    v.cross = v.carry = false;
     if (v.B != pr.B) continue;
     v.stream = p->stream;
     v.profile = false;
@@ -2487,7 +2551,7 @@ gmg_status gmg_solve(gmg_plan *p, double *u, const double *f, double rtol, int m
       } else if (p->cross) {
         HIPCHK(enqueue_cross_body(p, enq, u, f, act));
       } else if (!mixed) {
-        HIPCHK(enqueue_vcycle<double>(p, u, f, u, p->partials, act));
+        HIPCHK(enqueue_vcycle<double>(p, u, f, u, p->partials, act, enq > 0));
       } else {
         // body k: x_k = x_{k-1} + e (k >= 1), r32 = f - A x_k, norm, stop
         // test, then the FP32 cycle(s) for the next correction.  Iterates
@@ -2623,15 +2687,16 @@ gmg_status gmg_plan_set_tile(gmg_plan *p, int level, int stages, int variant, in
   const int tzv = tz > 0 ? std::min(tz, p->m[level]) : auto_tz(p->dim, p->m[level], stages, t);
   if (pass_geometry(p->dim, p->m[level], stages, t, tzv).nblocks > kMaxPartials)
     return GMG_ERR_INVALID_ARG;
-  if (!wj && stages == 3) {  // the cross-cycle pass of level 0
+  if (!wj && stages == 3) {  // the cross-cycle or repeated pre-smoothing pass of level 0
     if (level != 0) return GMG_ERR_INVALID_ARG;
     // the tile must run the form the plan will use: the restriction folded
     // in when the plan allows it and the tile fits, the plain form otherwise
     const size_t elem = p->cfg.precision == GMG_MIXED_FP32_IR ? sizeof(float) : sizeof(double);
-    const bool fold = !(p->cfg.flags & GMG_NO_FUSED_RESTRICT) &&
+    const int form = p->carry ? F_NORM_IN : F_PROLONG;
+    const bool fold = !(p->cfg.flags & GMG_NO_FUSED_RESTRICT) && !(p->carry && p->cfg.nu1 > 2) &&
                       pass_geometry(p->dim, p->m[0], 3, t, tzv, true).nblocks <= kMaxPartials &&
-                      rb_pass_fits(p->dim, 3, variant, F_PROLONG | F_RESTRICT, elem);
-    if (!fold && !rb_pass_fits(p->dim, 3, variant, F_PROLONG, elem)) return GMG_ERR_INVALID_ARG;
+                      rb_pass_fits(p->dim, 3, variant, form | F_RESTRICT, elem);
+    if (!fold && !rb_pass_fits(p->dim, 3, variant, form, elem)) return GMG_ERR_INVALID_ARG;
     PassChoice &c = p->ch[0][2];
     c.var[3] = variant;
     c.tz[3] = tzv;
@@ -2669,7 +2734,7 @@ gmg_status gmg_plan_get_tile(const gmg_plan *p, int level, int role, int *stages
   const int wj = p->cfg.smoother == GMG_SMOOTH_WJ ? 1 : 0;
   int st;
   if (role == 2) {
-    if (level != 0 || !(p->cross || p->cross32)) return GMG_ERR_INVALID_ARG;
+    if (level != 0 || !(p->cross || p->cross32 || p->carry)) return GMG_ERR_INVALID_ARG;
     st = 3;
   } else {
     const int nu = role == 0 ? p->cfg.nu1 : p->cfg.nu2;

@@ -1017,10 +1017,15 @@ __global__ void __launch_bounds__(NT) k_wj_pass(PassArgs<T> arg, const PassArgs<
 // Three stages (black, red, black): the pass that ends one cycle's backward
 // V(1,1) post-smoothing and starts the next cycle's forward sweep.
 // (Tiles with an even row count run the plain form, odd ones the form with
-// the restriction folded in: its halo is one row taller on the high side.)
+// the restriction folded in: its halo is one row taller on the high side.
+// The last two have a 64 x 16 output, which divides the sides 2^k - 1 with no
+// remainder to speak of: 255^3 in chunks of 64 is one workgroup per CU.  511^3
+// pre-smoothing of a repeated cycle, folded: 37 x 25 takes 875 us, 34 x 29
+// takes 916 us.)
 #define GMG_RB3_S3(X) \
   X(3, 3, 34, 30, 1024) X(3, 3, 36, 28, 1024) X(3, 3, 66, 30, 1024) X(3, 3, 34, 30, 512) \
-  X(3, 3, 66, 14, 512) X(3, 3, 34, 29, 1024) X(3, 3, 36, 27, 1024) X(3, 3, 33, 31, 1024)
+  X(3, 3, 66, 14, 512) X(3, 3, 34, 29, 1024) X(3, 3, 36, 27, 1024) X(3, 3, 33, 31, 1024) \
+  X(3, 3, 37, 25, 960) X(3, 3, 36, 24, 896)
 #define GMG_RB2_S3(X) X(2, 3, 64, 1, 64) X(2, 3, 128, 1, 128)
 #define GMG_RB2_S2(X) X(2, 2, 64, 1, 64) X(2, 2, 128, 1, 128)
 #define GMG_RB2_S4(X) X(2, 4, 64, 1, 64) X(2, 4, 128, 1, 128)
@@ -1184,9 +1189,10 @@ hipError_t run_wj(PassArgs<T> a, hipStream_t st, const PassArgs<T> *tbl, int nen
   }
 }  // namespace
 
-// The three-stage pass runs in two forms only: interpolated correction in,
-// mid-pass norm (FP64 solves) or none (the FP32 cycles of a refinement step),
-// with or without the folded restriction.
+// The three-stage pass runs in two uses, each with or without the folded
+// restriction: the cross-cycle pass (interpolated correction in, mid-pass
+// norm in FP64 solves, none in the FP32 cycles of a refinement step) and the
+// pre-smoothing of a repeated cycle (the norm of its input in FP64 solves).
 #define GMG_CROSS_SWITCH(RUN, T, D, S, E, Y, N)                                        \
   switch (flags) {                                                                  \
     case F_PROLONG | F_BLACK_FIRST | F_NORM_MID:                                    \
@@ -1194,6 +1200,10 @@ hipError_t run_wj(PassArgs<T> a, hipStream_t st, const PassArgs<T> *tbl, int nen
     case F_PROLONG | F_BLACK_FIRST | F_NORM_MID | F_RESTRICT:                       \
       return RUN<T, D, S, E, Y, N, F_PROLONG | F_BLACK_FIRST | F_NORM_MID | F_RESTRICT>(   \
           a, st, tbl, nent);                                                        \
+    case F_BLACK_FIRST | F_NORM_IN:                                                 \
+      return RUN<T, D, S, E, Y, N, F_BLACK_FIRST | F_NORM_IN>(a, st, tbl, nent);    \
+    case F_BLACK_FIRST | F_NORM_IN | F_RESTRICT:                                    \
+      return RUN<T, D, S, E, Y, N, F_BLACK_FIRST | F_NORM_IN | F_RESTRICT>(a, st, tbl, nent); \
     default: return hipErrorInvalidValue;                                           \
   }
 
@@ -1203,6 +1213,9 @@ hipError_t run_wj(PassArgs<T> a, hipStream_t st, const PassArgs<T> *tbl, int nen
       return RUN<T, D, S, E, Y, N, F_PROLONG | F_BLACK_FIRST>(a, st, tbl, nent);    \
     case F_PROLONG | F_BLACK_FIRST | F_RESTRICT:                                    \
       return RUN<T, D, S, E, Y, N, F_PROLONG | F_BLACK_FIRST | F_RESTRICT>(a, st, tbl, nent); \
+    case F_BLACK_FIRST: return RUN<T, D, S, E, Y, N, F_BLACK_FIRST>(a, st, tbl, nent); \
+    case F_BLACK_FIRST | F_RESTRICT:                                                \
+      return RUN<T, D, S, E, Y, N, F_BLACK_FIRST | F_RESTRICT>(a, st, tbl, nent);   \
     default: return hipErrorInvalidValue;                                           \
   }
 
