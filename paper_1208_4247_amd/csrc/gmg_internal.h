@@ -294,7 +294,9 @@ constexpr RbHalo rb_halo(int S, bool rst) {
 // LDS of a red-black pass and whether it fits the per-workgroup limit and
 // leaves a valid output tile (an even, positive row count in 3D)
 constexpr size_t kMaxPassLds = 160 * 1024;
-size_t rb_pass_lds_bytes(int dim, int stages, int exp_, int ey, int flags, size_t elem);
+// (elements of the pads before and after the planes: the farthest neighbour)
+constexpr int rb_lds_pad(int exp_) { return (exp_ + 2) & ~1; }
+size_t rb_pass_lds_bytes(int dim, int stages, int exp_, int ey, int nt, int flags, size_t elem);
 bool rb_pass_fits(int dim, int stages, int variant, int flags, size_t elem);
 // FNV-1a hash of the tile tables (shape of every variant index): part of the
 // autotuner's cache key, so a cached variant index never names another shape

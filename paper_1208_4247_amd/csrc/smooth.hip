@@ -47,6 +47,12 @@ template <typename T>
 __device__ __forceinline__ void pin_value(T &v) {
   asm volatile("" : "+v"(v) : : "memory");
 }
+// keep_branch: v is computed on this path only (a short uniform branch stays a
+// branch instead of selects on every path)
+template <typename T>
+__device__ __forceinline__ void keep_branch(T &v) {
+  asm volatile("" : "+v"(v));
+}
 __device__ __forceinline__ void compiler_fence() { asm volatile("" : : : "memory"); }
 
 // Tile index of workgroup bid of n.  Workgroups go to the 8 XCDs in turn and
@@ -183,7 +189,7 @@ __global__ void __launch_bounds__(NT) k_rb_pass(PassArgs<T> arg, const PassArgs<
   if (a.active && *gbl(a.active) == 0) return;
   constexpr int PL = EXP * EY;
   constexpr int NS = (PL + NT - 1) / NT;        // slots per thread
-  constexpr bool TAIL = NS * NT > PL;           // the last slot index has dead lanes
+  constexpr int PLS = NS * NT + 1;              // LDS plane: a slot for dead lanes too
   constexpr bool ZERO = (FL & F_ZERO_IN) != 0;
   constexpr bool PRO = (FL & F_PROLONG) != 0;
   constexpr bool NORM = (FL & F_NORM_IN) != 0;
@@ -216,18 +222,26 @@ __global__ void __launch_bounds__(NT) k_rb_pass(PassArgs<T> arg, const PassArgs<
   constexpr int CPL = NCX * NCY;
   constexpr int NCP = PRO ? (CPL + NT - 1) / NT : 1;
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  // [2 (step parity)][NB][PL]; RST: final plane and residual plane, each
-  // [2 (step parity)][2 (element)][PL]; PRO: [2][CPL]
-  T *lds = reinterpret_cast<T *>(smem_raw);
-  T *fwl = lds + 2 * NB * PL;
-  T *rl = fwl + 4 * PL;
-  T *cring = lds + 2 * NB * PL + (RST ? 8 * PL : 0);
+  // pad, [2 (step parity)][NB][PLS]; RST: final plane and residual plane, each
+  // [2 (step parity)][2 (element)][PLS]; PRO: [2][CPL]; pad.  The pads keep
+  // the neighbours of the first and last rows inside the allocation (their
+  // values are halo that nothing exact depends on), so no index is clamped.
+  // PLS is odd, and y + 1 has an index register of its own (ld): LDS accesses
+  // of one lane at a distance that a paired read or write can encode are
+  // otherwise merged by the compiler, and the paired forms conflict in the
+  // banks (cross-cycle pass at 1023^3, 33 x 31 tile: 6.72 ms; with the merges
+  // of an even stride 6.97 ms, of y - 1 and y + 1 6.88 ms)
+  constexpr int PAD = rb_lds_pad(EXP);
+  T *lds = reinterpret_cast<T *>(smem_raw) + PAD;
+  T *fwl = lds + 2 * NB * PLS;
+  T *rl = fwl + 4 * PLS;
+  T *cring = lds + 2 * NB * PLS + (RST ? 8 * PLS : 0);
 
   const int m = a.m;
   int tx, ty, tzc;
   tile_coords<DIM>(xcd_remap(blockIdx.x, a.nblocks, gsh), a.ntx, a.nty, a.sw, tx, ty, tzc);
   const int X0 = tx * 2 * TXP;
-  const bool xend = (m & 1) && X0 + 2 * TXP >= m;  // the output tile holds x = m - 1
+  const bool xend = X0 + 2 * (TXP + HPH) >= m;  // the extended tile holds x = m - 1 (m is odd)
   const int Y0 = ty * TY;
   const int Z0 = tzc * a.tz;
   const int Z1 = min(Z0 + a.tz, m);
@@ -239,60 +253,53 @@ __global__ void __launch_bounds__(NT) k_rb_pass(PassArgs<T> arg, const PassArgs<
   // has colour (e + par + z) & 1.
   // Loads take both elements of a pair at once from byte offset o2 (kOOB
   // when neither is inside the grid); the pair at the end of a row (xb =
-  // m - 1, m odd) loads elements (xb - 1, xb) instead, so element 0 is then
-  // the high half.  hP / hQ: element P / Q is the high half of the load.
+  // m - 1, m odd; rowend) loads elements (xb - 1, xb) instead, so element 0
+  // is then the high half.
   int o2[NS];
-  bool hP[NS], hQ[NS];
+  bool rowend[NS], hP[NS], hQ[NS];
   // stores: a pair of the output tile with both elements in the grid takes
-  // one 16-byte store at w2; the lone element of a row-end pair (m odd) an
-  // 8-byte store at w1 (kOOB elsewhere)
-  int w2[NS], w1[NS];
+  // one 16-byte store at w2 (kOOB elsewhere); the lone element of a row-end
+  // pair (w1) an 8-byte store
+  int w2[NS];
+  bool w1[NS];
   bool nP[NS], nQ[NS];   // NORM: element inside the grid and the output tile
   bool kP[NS], kQ[NS];   // element inside the grid
-  int lq[NS], lP[NS], lQ[NS], lu[NS], ld[NS];  // LDS: self, x-side of P / Q, y-1, y+1
-  bool live[NS];
+  int lq[NS], lP[NS], lQ[NS], ld[NS];  // LDS: self, x-side of P / Q, y+1 (y-1: self - EXP)
   int cb[PRO ? NS : 1];
   bool c2[PRO ? NS : 1];
   bool pone[NS];  // element P is element 1 of the pair
-  bool k0[RST ? NS : 1], k1[RST ? NS : 1];  // element 0 / 1 inside the grid
 #pragma unroll
   for (int i = 0; i < NS; ++i) {
     const int q = threadIdx.x + NT * i;
-    live[i] = q < PL;
-    const int qc = live[i] ? q : PL - 1;
-    const int p = qc % EXP, r = qc / EXP;
+    const bool live = q < PL;
+    const int p = q % EXP, r = q / EXP;
     const int xb = X0 - 2 * HPL + 2 * p;
     const int y = DIM == 3 ? Y0 - HYL + r : 0;
     const bool yin = DIM == 2 || (y >= 0 && y < m);
     const int par = (y + DIM) & 1;
     const int off = (DIM == 3 ? y * m : 0) + xb;
-    const bool in0 = live[i] && yin && xb >= 0 && xb < m;
-    const bool in1 = live[i] && yin && xb + 1 >= 0 && xb + 1 < m;
-    const bool outp = live[i] && yin && p >= HPL && p < HPL + TXP &&
+    const bool in0 = live && yin && xb >= 0 && xb < m;
+    const bool in1 = live && yin && xb + 1 >= 0 && xb + 1 < m;
+    const bool outp = live && yin && p >= HPL && p < HPL + TXP &&
                       (DIM == 2 || (r >= HYL && r < HYL + TY)) && xb < m;
     const int o0 = in0 ? off * (int)sizeof(T) : kOOB;
-    const int o1 = in1 ? (off + 1) * (int)sizeof(T) : kOOB;
     const bool half = in0 && !in1;
     o2[i] = in0 ? (off - (half ? 1 : 0)) * (int)sizeof(T) : kOOB;
-    hP[i] = par ? true : half;
-    hQ[i] = par ? half : true;
+    rowend[i] = half;
+    hP[i] = par || half;
+    hQ[i] = !par || half;
     kP[i] = par ? in1 : in0;
     kQ[i] = par ? in0 : in1;
     w2[i] = (outp && in1) ? o0 : kOOB;
-    w1[i] = (outp && half) ? o0 : kOOB;
+    w1[i] = outp && half;
     nP[i] = outp && kP[i];
     nQ[i] = outp && kQ[i];
-    lq[i] = qc;
-    const int left = max(qc - 1, 0), right = min(qc + 1, PL - 1);
-    lP[i] = par ? right : left;  // element 1 updates from the pair to its right
-    lQ[i] = par ? left : right;
-    lu[i] = max(qc - EXP, 0);
-    ld[i] = min(qc + EXP, PL - 1);
+    lq[i] = q;
+    ld[i] = q + EXP;
+    keep_branch(ld[i]);
+    lP[i] = par ? q + 1 : q - 1;  // element 1 updates from the pair to its right
+    lQ[i] = par ? q - 1 : q + 1;
     pone[i] = par != 0;
-    if (RST) {
-      k0[i] = in0;
-      k1[i] = in1;
-    }
     if (PRO) {
       const int rr = DIM == 3 ? r : 0;
       c2[i] = DIM == 3 && !(rr & 1);
@@ -302,7 +309,7 @@ __global__ void __launch_bounds__(NT) k_rb_pass(PassArgs<T> arg, const PassArgs<
 
   T W[S][NS][3];  // stage windows: [0] newest plane, [1] previous, [2] two back
   T WB[NORM ? NS : 1][3];
-  T pu0[NS], pu1[NS];  // start value of the plane being entered (elements P, Q)
+  T pu0[NS], pu1[NS];  // start value of the plane being entered (elements 0, 1)
 #pragma unroll
   for (int s = 0; s < S; ++s)
 #pragma unroll
@@ -313,8 +320,7 @@ __global__ void __launch_bounds__(NT) k_rb_pass(PassArgs<T> arg, const PassArgs<
 
   // RST: coarse planes c with fine centre 2c+1 in [Z0, Z1) belong to this
   // chunk; their residual planes are 2*CZ0 .. 2*CZ1
-  const int mc = a.mc;
-  const int CZ0 = Z0 >> 1, CZ1 = min(Z1 >> 1, mc);
+  const int CZ0 = Z0 >> 1, CZ1 = min(Z1 >> 1, a.mc);
   // steps in pairs from an even start; the extra leading or trailing step
   // only touches planes outside the exact region
   const int t0 = (Z0 - S - (RST ? 2 : 0)) & ~1;
@@ -329,20 +335,25 @@ __global__ void __launch_bounds__(NT) k_rb_pass(PassArgs<T> arg, const PassArgs<
   // only unpacked (element choice, zero boundary) when their plane is used,
   // so nothing waits on a load early.
   PairOf<T> uR[2][ZERO ? 1 : NS], fR[2][NS];
+  const int mc = a.mc;
+  const int cplane = DIM == 3 ? mc * mc : mc;
   auto issue_u = [&](int t, PairOf<T> *v) {
     if (ZERO) return;
     const __amdgpu_buffer_rsrc_t r = plane_rsrc(a.u_in, t, m, planeS);
 #pragma unroll
     for (int i = 0; i < NS; ++i) v[i] = bload2<T>(r, o2[i]);
   };
-  auto take_u = [&](const PairOf<T> *v, T *v0, T *v1) {
+  // elements 0 / 1 of the raw pairs; outside the grid (zero loads) they are 0
+  auto take = [&](const PairOf<T> *v, T *v0, T *v1) {
 #pragma unroll
     for (int i = 0; i < NS; ++i) {
-      if (ZERO) {
-        v0[i] = v1[i] = T(0);
-      } else {
-        v0[i] = kP[i] ? (hP[i] ? v[i].hi : v[i].lo) : T(0);
-        v1[i] = kQ[i] ? (hQ[i] ? v[i].hi : v[i].lo) : T(0);
+      v0[i] = v[i].lo;
+      v1[i] = v[i].hi;
+      if (xend) {  // a real (uniform) branch: tiles away from the row ends skip it
+        v0[i] = rowend[i] ? v[i].hi : v[i].lo;
+        v1[i] = rowend[i] ? T(0) : v[i].hi;
+        keep_branch(v0[i]);
+        keep_branch(v1[i]);
       }
     }
   };
@@ -351,6 +362,8 @@ __global__ void __launch_bounds__(NT) k_rb_pass(PassArgs<T> arg, const PassArgs<
 #pragma unroll
     for (int i = 0; i < NS; ++i) v[i] = bload2<T>(r, o2[i]);
   };
+  // f as elements P / Q (hP, hQ: the high half of the load); outside the grid
+  // it may hold anything, nothing there reads it
   auto take_f = [&](const PairOf<T> *v, T *vP, T *vQ) {
 #pragma unroll
     for (int i = 0; i < NS; ++i) {
@@ -369,7 +382,6 @@ __global__ void __launch_bounds__(NT) k_rb_pass(PassArgs<T> arg, const PassArgs<
   // rows r / 2 and r / 2 + 1.
   const int CX0 = ((X0 - 2 * HPL) >> 1) - 1;
   const int CY0 = DIM == 3 ? ((Y0 - HYL) >> 1) - 1 : 0;
-  const int cplane = DIM == 3 ? mc * mc : mc;
   int coff[NCP];
   if (PRO) {
 #pragma unroll
@@ -400,12 +412,16 @@ __global__ void __launch_bounds__(NT) k_rb_pass(PassArgs<T> arg, const PassArgs<
     const T el = P[0], er = P[1];
     v0 = T(0.5) * (el + er);
     v1 = er;
-    if (c2[i]) {
+    if (DIM == 3) {  // rows of both kinds share a wavefront: no branch
       const T fl = P[NCX], fr = P[NCX + 1];
-      v0 = T(0.5) * (v0 + T(0.5) * (fl + fr));
-      v1 = T(0.5) * (v1 + fr);
+      const T b0 = T(0.5) * (v0 + T(0.5) * (fl + fr)), b1 = T(0.5) * (v1 + fr);
+      v0 = c2[i] ? b0 : v0;
+      v1 = c2[i] ? b1 : v1;
     }
   };
+  // xy-interpolated correction from the coarse plane below plane t (t even)
+  // or at it (t odd)
+  T ck0[PRO ? NS : 1], ck1[PRO ? NS : 1];
   if (PRO) {
     // coarse planes t0 / 2 - 1 and t0 / 2 (t0 is even)
     T cv[NCP];
@@ -414,6 +430,8 @@ __global__ void __launch_bounds__(NT) k_rb_pass(PassArgs<T> arg, const PassArgs<
     load_c(t0 >> 1, cv);
     store_c(t0 >> 1, cv);
     __syncthreads();
+#pragma unroll
+    for (int i = 0; i < NS; ++i) cxy((t0 >> 1) - 1, i, ck0[i], ck1[i]);
   }
 
   // right-hand side window: fP[j] / fQ[j] hold elements P / Q of f on plane
@@ -427,12 +445,13 @@ __global__ void __launch_bounds__(NT) k_rb_pass(PassArgs<T> arg, const PassArgs<
     issue_f(t0 - j, v);
     take_f(v, fP[j], fQ[j]);
   }
-  // RST: final values (elements 0 / 1) of planes t-S, t-S-1, t-S-2, and the
-  // full-weighting accumulator of this thread's coarse point
-  T fw0[RST ? NS : 1][3], fw1[RST ? NS : 1][3];
+  // RST: the last stage's values of planes t-S-1, t-S-2 (its colour of the
+  // final iterate; the other colour is stage S-1's, in W except for the
+  // oldest plane), and the full-weighting accumulator of this thread's coarse
+  // point
+  T fS1[RST ? NS : 1], fS2[RST ? NS : 1], wS3[RST ? NS : 1];
 #pragma unroll
-  for (int i = 0; i < (RST ? NS : 1); ++i)
-    fw0[i][0] = fw0[i][1] = fw0[i][2] = fw1[i][0] = fw1[i][1] = fw1[i][2] = T(0);
+  for (int i = 0; i < (RST ? NS : 1); ++i) fS1[i] = fS2[i] = wS3[i] = T(0);
   constexpr int NCC = DIM == 3 ? TXP * (TY / 2) : TXP;  // coarse points of the tile
   const int ccx = threadIdx.x % TXP, ccy = DIM == 3 ? threadIdx.x / TXP : 0;
   const int cgx = (X0 >> 1) + ccx, cgy = DIM == 3 ? (Y0 >> 1) + ccy : 0;
@@ -447,13 +466,20 @@ __global__ void __launch_bounds__(NT) k_rb_pass(PassArgs<T> arg, const PassArgs<
 
   auto step = [&](int t, auto tp_tag) {
     constexpr int TP = decltype(tp_tag)::value;  // t & 1
+    auto in_grid = [&](int z) { return z >= 0 && z < m; };
+    auto in_chunk = [&](int z) { return z >= Z0 && z < Z1; };
     auto isP = [](int s) { return (((C1 + s - 1) + TP - s) & 1) == 0; };
     constexpr bool B0P = ((C0 + TP - 1) & 1) == 0;  // colour-C0 element of plane t-1 is P
     const int zr = t - 1;
-    const bool rin = NORM && zr >= Z0 && zr < Z1;
+    const bool rin = NORM && in_chunk(zr);
     // plane t: start value and right-hand side from the raw loads of step
     // t - 2, then plane t + 2's loads into the same registers
-    take_u(uR[TP], pu0, pu1);
+    if (ZERO) {
+#pragma unroll
+      for (int i = 0; i < NS; ++i) pu0[i] = pu1[i] = T(0);
+    } else {
+      take(uR[TP], pu0, pu1);
+    }
 #pragma unroll
     for (int j = NF - 1; j >= 1; --j)
 #pragma unroll
@@ -471,7 +497,7 @@ __global__ void __launch_bounds__(NT) k_rb_pass(PassArgs<T> arg, const PassArgs<
     }
     issue_u(t + 2, uR[TP]);
     issue_f(t + 2, fR[TP]);
-    const T *Lprev = lds + (1 - TP) * NB * PL;  // planes published at step t-1
+    const T *Lprev = lds + (1 - TP) * NB * PLS;  // planes published at step t-1
 
     // ---- RST: full weighting of the residual plane t-S-2 (published at step
     // t-1) onto this thread's coarse point: in-plane x, then y, then the
@@ -481,14 +507,17 @@ __global__ void __launch_bounds__(NT) k_rb_pass(PassArgs<T> arg, const PassArgs<
       const bool use = cown && zf >= 2 * CZ0 && zf <= 2 * CZ1;
       T sxy = T(0);
       if (use) {
-        const T *R0 = rl + (1 - TP) * 2 * PL, *R1 = R0 + PL;
-        auto row = [&](int q) {
+        // a coarse row's fine row has par = 0 (P = element 0), the rows next
+        // to it the other way round
+        const T *RP = rl + (1 - TP) * 2 * PLS, *RQ = RP + PLS;
+        auto row = [&](const T *R0, const T *R1, int q) {
           return T(0.25) * R0[q] + T(0.5) * R1[q] + T(0.25) * R0[q + 1];
         };
         if (DIM == 3)
-          sxy = T(0.25) * row(cq - EXP) + T(0.5) * row(cq) + T(0.25) * row(cq + EXP);
+          sxy = T(0.25) * row(RQ, RP, cq - EXP) + T(0.5) * row(RP, RQ, cq) +
+                T(0.25) * row(RQ, RP, cq + EXP);
         else
-          sxy = row(cq);
+          sxy = row(RP, RQ, cq);
       }
       if constexpr (((TP + S) & 1) != 0) {
         if (use) cacc += T(0.5) * sxy;
@@ -505,25 +534,24 @@ __global__ void __launch_bounds__(NT) k_rb_pass(PassArgs<T> arg, const PassArgs<
 
     // ---- stage 0: start value on plane t (colour C0 into the window)
     constexpr bool S0P = ((C0 + TP) & 1) == 0;  // colour-C0 element of plane t is P
-    const bool tin = t >= 0 && t < m;
 #pragma unroll
     for (int i = 0; i < NS; ++i) {
-      T vP = pu0[i], vQ = pu1[i];
+      T v0 = pu0[i], v1 = pu1[i];
       if (PRO) {
-        T c0, c1;
-        if (TP == 1) {  // fine node t+1 even: on coarse plane (t-1)/2
-          cxy((t - 1) >> 1, i, c0, c1);
-        } else {        // between coarse planes t/2-1 and t/2
-          T l0, l1, h0, h1;
-          cxy((t >> 1) - 1, i, l0, l1);
-          cxy(t >> 1, i, h0, h1);
-          c0 = T(0.5) * (l0 + h0);
-          c1 = T(0.5) * (l1 + h1);
+        // t even: between coarse planes t/2-1 (kept from the step before) and
+        // t/2; t odd (fine node t+1 even): on coarse plane (t-1)/2, kept.
+        // Outside the grid the correction is 0: every such node lies on or
+        // between coarse nodes that read as 0.
+        T c0 = ck0[i], c1 = ck1[i];
+        if (TP == 0) {
+          cxy(t >> 1, i, ck0[i], ck1[i]);
+          c0 = T(0.5) * (c0 + ck0[i]);
+          c1 = T(0.5) * (c1 + ck1[i]);
         }
-        const T cP = pone[i] ? c1 : c0, cQ = pone[i] ? c0 : c1;
-        vP = (tin && kP[i]) ? vP + cP : vP;
-        vQ = (tin && kQ[i]) ? vQ + cQ : vQ;
+        v0 += c0;
+        v1 += c1;
       }
+      const T vP = pone[i] ? v1 : v0, vQ = pone[i] ? v0 : v1;
       W[0][i][2] = W[0][i][1];
       W[0][i][1] = W[0][i][0];
       W[0][i][0] = S0P ? vP : vQ;
@@ -536,7 +564,7 @@ __global__ void __launch_bounds__(NT) k_rb_pass(PassArgs<T> arg, const PassArgs<
     // ---- residual of the start value on plane t-1 (convergence test)
     if (NORM && rin) {
       const T *L0 = Lprev;           // colour C0 values of plane t-1
-      const T *LB = Lprev + S * PL;  // colour C1 values of plane t-1
+      const T *LB = Lprev + S * PLS;  // colour C1 values of plane t-1
 #pragma unroll
       for (int i = 0; i < NS; ++i) {
 #pragma unroll
@@ -547,7 +575,7 @@ __global__ void __launch_bounds__(NT) k_rb_pass(PassArgs<T> arg, const PassArgs<
           const T *Ln = c == 0 ? LB : L0;
           T nb = own + Ln[eP ? lP[i] : lQ[i]];
           if (DIM == 3) {
-            nb += Ln[lu[i]];
+            nb += Ln[lq[i] - EXP];
             nb += Ln[ld[i]];
           }
           nb += c == 0 ? WB[i][2] : W[0][i][2];
@@ -564,13 +592,13 @@ __global__ void __launch_bounds__(NT) k_rb_pass(PassArgs<T> arg, const PassArgs<
 #pragma unroll
     for (int s = 1; s <= S; ++s) {
       const int zs = t - s;
-      const bool zin = zs >= 0 && zs < m;
-      const T *L = Lprev + (s - 1) * PL;
+      const bool zin = in_grid(zs);
+      const T *L = Lprev + (s - 1) * PLS;
 #pragma unroll
       for (int i = 0; i < NS; ++i) {
         T nb = W[s - 1][i][1] + L[isP(s) ? lP[i] : lQ[i]];  // x-1 and x+1 (one is the own pair)
         if (DIM == 3) {
-          nb += L[lu[i]];  // y - 1
+          nb += L[lq[i] - EXP];  // y - 1
           nb += L[ld[i]];  // y + 1
         }
         nb += W[s - 1][i][2];  // marching axis - 1
@@ -582,7 +610,7 @@ __global__ void __launch_bounds__(NT) k_rb_pass(PassArgs<T> arg, const PassArgs<
           // the updated colour's residual after stage QN, from the same
           // neighbour sum: plane t - QN
           const double r = double(fv) - (double(T(2 * DIM) * v) - double(nb)) * a.inv_h2;
-          const bool use = zs >= Z0 && zs < Z1 && (isP(s) ? nP[i] : nQ[i]);
+          const bool use = in_chunk(zs) && (isP(s) ? nP[i] : nQ[i]);
           acc += use ? r * r : 0.0;
         }
         if (s < S) {
@@ -600,14 +628,14 @@ __global__ void __launch_bounds__(NT) k_rb_pass(PassArgs<T> arg, const PassArgs<
     // neighbour order x-1, x+1, y-1, y+1, z-1, z+1 as in the stages
     if (NMID) {
       const int zb = t - QN - 1;
-      const bool bin = zb >= Z0 && zb < Z1;
-      const T *Lq = Lprev + QN * PL;  // stage QN's plane zb (published at step t-1)
+      const bool bin = in_chunk(zb);
+      const T *Lq = Lprev + QN * PLS;  // stage QN's plane zb (published at step t-1)
       constexpr bool EP = isP(QN - 1);     // the colour of stage QN - 1 is element P
 #pragma unroll
       for (int i = 0; i < NS; ++i) {
         T nb = W[QN][i][1] + Lq[EP ? lP[i] : lQ[i]];
         if (DIM == 3) {
-          nb += Lq[lu[i]];
+          nb += Lq[lq[i] - EXP];
           nb += Lq[ld[i]];
         }
         nb += W[QN][i][2];
@@ -624,69 +652,65 @@ __global__ void __launch_bounds__(NT) k_rb_pass(PassArgs<T> arg, const PassArgs<
     // of odd side adds the 8-byte store of its row-end elements)
     const int zo = t - S;
     {
-      const __amdgpu_buffer_rsrc_t r = plane_rsrc_if(a.u_out, zo, zo >= Z0 && zo < Z1, planeS);
+      const __amdgpu_buffer_rsrc_t r = plane_rsrc_if(a.u_out, zo, in_chunk(zo), planeS);
 #pragma unroll
       for (int i = 0; i < NS; ++i) {
         const T vP = isP(S) ? newS[i] : W[S - 1][i][1];
         const T vQ = isP(S) ? W[S - 1][i][1] : newS[i];
         const T e0 = pone[i] ? vQ : vP, e1 = pone[i] ? vP : vQ;
         bstore2<T>(r, w2[i], e0, e1);
-        if (xend) bstore<T>(r, w1[i], e0);
+        // (a row-end pair was loaded from one element before it)
+        if (xend) bstore<T>(r, w1[i] ? o2[i] + (int)sizeof(T) : kOOB, e0);
       }
     }
-    // ---- RST: final values of plane t-S into the window; residual of plane
-    // t-S-1 (same expression as the separate restriction kernel: neighbours
-    // x-1, x+1, y-1, y+1, z-1, z+1 in that order)
-    T *FWnow = fwl + TP * 2 * PL;
-    T *Rnow = rl + TP * 2 * PL;
+    // ---- RST: final values of plane t-S; residual of plane t-S-1 (same
+    // expression as the separate restriction kernel: neighbours x-1, x+1,
+    // y-1, y+1, z-1, z+1 in that order).  The full weighting reads points of
+    // the grid only, so nothing is masked.
+    T *FWnow = fwl + TP * 2 * PLS;
+    T *Rnow = rl + TP * 2 * PLS;
     if (RST) {
-      const T *F0 = fwl + (1 - TP) * 2 * PL, *F1 = F0 + PL;  // plane t-S-1
-      const int zw = t - S - 1;
-      const bool win = zw >= 0 && zw < m;
+      const T *FP = fwl + (1 - TP) * 2 * PLS, *FQ = FP + PLS;  // plane t-S-1
       const T inv_h2 = T(a.inv_h2);
+      constexpr bool SP = isP(S);  // stage S's colour of plane t-S is element P
 #pragma unroll
       for (int i = 0; i < NS; ++i) {
-        const T vP = isP(S) ? newS[i] : W[S - 1][i][1];
-        const T vQ = isP(S) ? W[S - 1][i][1] : newS[i];
-        fw0[i][2] = fw0[i][1];
-        fw0[i][1] = fw0[i][0];
-        fw0[i][0] = pone[i] ? vQ : vP;
-        fw1[i][2] = fw1[i][1];
-        fw1[i][1] = fw1[i][0];
-        fw1[i][0] = pone[i] ? vP : vQ;
         const int q = lq[i];
-        const int left = max(q - 1, 0), right = min(q + 1, PL - 1);
-        const T f0 = pone[i] ? fQ[S + 1][i] : fP[S + 1][i];
-        const T f1 = pone[i] ? fP[S + 1][i] : fQ[S + 1][i];
-        T nb0 = F1[left] + fw1[i][1];
-        T nb1 = fw0[i][1] + F0[right];
+        // final values, elements P / Q: planes t-S (z+1), t-S-1, t-S-2 (z-1)
+        const T aP = SP ? newS[i] : W[S - 1][i][1], aQ = SP ? W[S - 1][i][1] : newS[i];
+        const T bP = SP ? W[S - 1][i][2] : fS1[i], bQ = SP ? fS1[i] : W[S - 1][i][2];
+        const T dP = SP ? fS2[i] : wS3[i], dQ = SP ? wS3[i] : fS2[i];
+        // the x neighbours of an element are the other elements of its own
+        // pair and of the pair next to it, the y neighbours the other
+        // elements of the rows next to it
+        T nbP = bQ + FQ[lP[i]], nbQ = bP + FP[lQ[i]];
         if (DIM == 3) {
-          nb0 += F0[lu[i]];
-          nb0 += F0[ld[i]];
-          nb1 += F1[lu[i]];
-          nb1 += F1[ld[i]];
+          nbP += FQ[q - EXP];
+          nbP += FQ[ld[i]];
+          nbQ += FP[q - EXP];
+          nbQ += FP[ld[i]];
         }
-        nb0 += fw0[i][2];
-        nb0 += fw0[i][0];
-        nb1 += fw1[i][2];
-        nb1 += fw1[i][0];
-        const T r0 = f0 - (T(2 * DIM) * fw0[i][1] - nb0) * inv_h2;
-        const T r1 = f1 - (T(2 * DIM) * fw1[i][1] - nb1) * inv_h2;
-        if (TAIL && i == NS - 1 && !live[i]) continue;
-        Rnow[q] = (win && k0[i]) ? r0 : T(0);
-        Rnow[PL + q] = (win && k1[i]) ? r1 : T(0);
-        FWnow[q] = fw0[i][0];
-        FWnow[PL + q] = fw1[i][0];
+        nbP += dP;
+        nbP += aP;
+        nbQ += dQ;
+        nbQ += aQ;
+        T *Rn = Rnow + q, *Fn = FWnow + q;
+        Rn[0] = fP[S + 1][i] - (T(2 * DIM) * bP - nbP) * inv_h2;
+        Rn[PLS] = fQ[S + 1][i] - (T(2 * DIM) * bQ - nbQ) * inv_h2;
+        Fn[0] = aP;
+        Fn[PLS] = aQ;
+        fS2[i] = fS1[i];
+        fS1[i] = newS[i];
+        wS3[i] = W[S - 1][i][2];
       }
     }
     // ---- publish the newest plane of every stage for step t+1
-    T *Lnow = lds + TP * NB * PL;
+    T *Lnow = lds + TP * NB * PLS;
 #pragma unroll
     for (int i = 0; i < NS; ++i) {
-      if (TAIL && i == NS - 1 && !live[i]) continue;
 #pragma unroll
-      for (int s = 0; s < S; ++s) Lnow[s * PL + lq[i]] = W[s][i][0];
-      if (NORM) Lnow[S * PL + lq[i]] = WB[i][0];
+      for (int s = 0; s < S; ++s) Lnow[s * PLS + lq[i]] = W[s][i][0];
+      if (NORM) Lnow[S * PLS + lq[i]] = WB[i][0];
     }
     if (PRO && TP == 1) {
       store_c((t + 1) >> 1, cnext);
@@ -1102,9 +1126,10 @@ uint32_t tile_table_hash() {
   return h;
 }
 
-size_t rb_pass_lds_bytes(int dim, int stages, int exp_, int ey, int flags, size_t elem) {
-  const size_t pl = (size_t)exp_ * ey;
-  size_t n = 2 * pl * (size_t)(stages + ((flags & F_NORM_IN) ? 1 : 0));
+size_t rb_pass_lds_bytes(int dim, int stages, int exp_, int ey, int nt, int flags, size_t elem) {
+  // planes hold a slot for every lane (exp_ * ey rounded up to the workgroup)
+  const size_t pl = ((size_t)exp_ * ey + nt - 1) / nt * nt + 1;
+  size_t n = 2 * pl * (size_t)(stages + ((flags & F_NORM_IN) ? 1 : 0)) + 2 * rb_lds_pad(exp_);
   if (flags & F_RESTRICT) n += 8 * pl;
   if (flags & F_PROLONG) n += 2 * (size_t)(exp_ + 1) * (dim == 3 ? (ey + 1) / 2 + 1 : 1);
   return n * elem;
@@ -1116,7 +1141,7 @@ bool rb_pass_fits(int dim, int stages, int variant, int flags, size_t elem) {
   const RbHalo h = rb_halo(stages, (flags & F_RESTRICT) != 0);
   const int txp = t.exp_ - h.pl - h.ph, ty = dim == 3 ? t.ey - h.yl - h.yh : 2;
   return txp > 0 && ty > 0 && ty % 2 == 0 &&
-         rb_pass_lds_bytes(dim, stages, t.exp_, t.ey, flags, elem) <= kMaxPassLds;
+         rb_pass_lds_bytes(dim, stages, t.exp_, t.ey, t.nt, flags, elem) <= kMaxPassLds;
 }
 
 PassGeom pass_geometry(int dim, int m, int stages, const PassTile &t, int tz, bool restrict_) {
@@ -1158,7 +1183,7 @@ hipError_t run_rb(PassArgs<T> a, hipStream_t st, const PassArgs<T> *tbl, int nen
   if constexpr (txp <= 0 || ty <= 0 || ty % 2 != 0) {
     return hipErrorInvalidValue;  // this tile does not run this form
   } else {
-  const size_t lds = rb_pass_lds_bytes(DIM, S, EXP, EY, FL, sizeof(T));
+  const size_t lds = rb_pass_lds_bytes(DIM, S, EXP, EY, NT, FL, sizeof(T));
   if (lds > kMaxPassLds) return hipErrorInvalidConfiguration;
   auto k = k_rb_pass<T, DIM, S, EXP, EY, NT, FL>;
   static int gsh = 0;
