@@ -1154,40 +1154,63 @@ int auto_tz(int dim, int m, int st, const PassTile &t) {
   return std::max(tzv, std::min(m, 8));
 }
 
-// Default pass choice for a level and role, from measurements on MI355X
-// (single-sweep passes win on small grids and for the prolongation pass;
-// two fused sweeps win for plain smoothing of large grids).
+// Default pass choice for a level and role: what the tuner picks on MI355X,
+// which depends on the size in a regular way (both sides of each line below as
+// measured, FP64 unless stated; the step is the pass and what follows it).
+//  * Two sweeps per pass wherever there are two: one pass of four stages
+//    against two of two stages is 17.4 against 2 x 10.7 us at 63^3, 7.0
+//    against 2 x 5.4 us at 255^2, and half the traffic on large grids.
+//  * z-chunks: short where a level cannot fill the chip otherwise (4 planes at
+//    63^3, 8 at 127^3: a chunk recomputes as many planes of halo, but its
+//    planes are a chain of latencies), then as long as one workgroup per CU
+//    allows (64 at 255^3).  The 127^3 V(1,1) cross-cycle pass takes 89 us in
+//    chunks of 4 with a large tile, 24 us in chunks of 8 with the 36 x 24 one.
+//  * The restriction folded into the last pre-smoothing pass: where its halo
+//    costs less than reading w and f again, which is large grids (255^3
+//    three-stage pass 126 against 90 + 60 us; at 127^3 the tuner keeps the
+//    two, 35 us together); not into the four-stage FP64 pass, which has no
+//    registers left for it (the tuner never folds it, 1266 us at 511^3).
 PassChoice choice_for(const gmg_config &cfg, int dim, int m, int role, int smax_cap) {
   PassChoice c;
   const bool wj = cfg.smoother == GMG_SMOOTH_WJ;
-  const bool big = dim == 3 ? m >= 255 : m >= 2047;
-  c.smax = std::min(smax_cap, (big && role == 0) ? 2 : 1);
-  if (dim == 2) c.smax = std::min(smax_cap, 2);
+  const bool fp32 = cfg.precision == GMG_MIXED_FP32_IR;
+  const bool may_fold = !wj && !(cfg.flags & GMG_NO_FUSED_RESTRICT);
+  c.smax = smax_cap;
+  if (dim == 3)
+    c.fuse = role == 2 ? m >= 255 : (cfg.nu1 == 1 ? m >= 255 : fp32 && m >= 511);
+  else
+    c.fuse = fp32 || m >= (role == 0 && cfg.nu1 == 1 ? 127 : 255);
   for (int st = 1; st <= 4; ++st) {
     const int nv = pass_variant_count(dim, st, wj ? 1 : 0);
     if (nv == 0) continue;
     int v = 0, tz = 0;
-    if (dim == 3 && !wj) {
-      if (m <= 127) {
-        v = st == 2 ? 2 : 1;  // (66,14,512) / (36,24,256)
-        tz = m <= 63 ? 2 : 4;
-      } else if (m <= 255) {
-        v = 1;
-        tz = 32;
-      } else {
-        v = 0;
-        tz = st == 4 ? 0 : 32;
-      }
+    if (dim == 2) {
+      tz = m <= 511 ? 4 : m <= 1023 ? 12 : m <= 2047 ? 16 : 64;
     } else {
-      v = (m >= 255 || nv == 1) ? 0 : 1;
+      tz = m <= 15 ? 2 : m <= 31 ? 3 : m <= 63 ? 4 : m <= 127 ? 8 : m <= 255 ? 64 : m <= 511 ? 256 : 341;
+      if (wj) {
+        v = m <= 63 ? 2 : m <= 127 || (st == 1 && m >= 511) ? 1 : 0;
+        if (m >= 255) tz = m <= 255 ? 43 : st == 1 ? 86 : 171;
+      } else if (st == 2) {
+        // 34 x 30 pairs for 1024 threads; the large post-passes and FP32
+        // passes two slots per thread (66 x 30), small FP32 ones 66 x 14
+        v = fp32 ? (m <= 127 ? 2 : 0) : (role == 1 && m >= 511 ? 0 : 3);
+        if (fp32 && m == 255) tz = 22;
+      } else if (st == 3) {
+        // folded: 64 x 16 output (37 x 25 pairs), 56 x 22 on the largest
+        // grids; plain: 36 x 24 for 896 threads
+        const bool fold = c.fuse && may_fold;
+        v = !fold ? 9 : m >= 1023 ? 7 : 8;
+        if (fold && m >= 1023) tz = 512;
+        if (fp32 && m == 255) tz = 32;
+      } else {
+        v = 3;  // 36 x 24 for 896 threads
+        if (m == 255 && (role == 0 || fp32)) tz = 32;
+      }
     }
-    // the three-stage pass: a tile that runs the form with the restriction
-    // folded in (odd row count)
-    if (st == 3 && dim == 3 && !wj) v = 5;
     v = std::min(v, nv - 1);
     c.var[st] = v;
-    const PassTile t = pass_variant(dim, st, wj ? 1 : 0, v);
-    c.tz[st] = tz > 0 ? std::min(tz, m) : auto_tz(dim, m, st, t);
+    c.tz[st] = std::min(tz, m);
   }
   return c;
 }
