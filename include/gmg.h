@@ -323,12 +323,14 @@ typedef struct gmg_dst gmg_dst; /* opaque, host side */
  * sin^2(k_i pi h / 2) (exact up to rounding).  Two-phase like gmg_setup:
  * with workspace == NULL only *ws_bytes is written.  Otherwise workspace
  * (device memory, 256-byte aligned, at least *ws_bytes bytes, caller-owned)
- * holds the odd extensions and the FFT coefficients of every line and the
- * FFT library's work area (about 4 grids in all).  dim 2 (levels <= 14) or 3
- * (levels <= 10).  stream: a hipStream_t (NULL = default).  The batched FFTs
- * are rocFFT's; plan creation may compile FFT kernels on first use, and the
- * plan keeps twiddle tables in device memory that rocFFT allocates itself
- * (released by gmg_dst_destroy).  Errors:
+ * holds the tables of the transform (at most 164 KB; the setup uploads them on
+ * the stream, and gmg_dst_solve works in place in u).  dim 2 (levels <= 14) or
+ * 3 (levels <= 10).  stream: a hipStream_t (NULL = default).  2D with levels
+ * >= 13 and one-node grids (levels 1) run rocFFT's batched FFTs instead: there
+ * the workspace holds the odd extensions and the FFT coefficients of every
+ * line (about 4 grids), plan creation may compile FFT kernels on first use,
+ * and the plan keeps twiddle tables in device memory that rocFFT allocates
+ * itself (released by gmg_dst_destroy).  Errors:
  * GMG_ERR_INVALID_ARG, GMG_ERR_WORKSPACE, GMG_ERR_HIP (FFT library failure). */
 gmg_status gmg_dst_setup(int dim, int levels, void *workspace, size_t *ws_bytes, void *stream,
                          gmg_dst **out);

@@ -29,11 +29,20 @@
 // The last forward pass divides by the eigenvalues and applies the inverse's
 // scale (2/(m+1))^d (DST-I is its own inverse up to (m+1)/2 per axis); d
 // more passes invert the transform.  FP64 throughout.
+//
+// That is the general path (a line's FFT longer than the LDS holds, 2D beyond
+// 4095^2, and the one-node grids).  Everything else takes the axis kernel
+// (k_dst_axis): one launch transforms every line along one axis, with the
+// whole FFT of a pair of lines in LDS, in place in u.  Nothing is packed,
+// extended or transposed in memory, so a pass moves 16 B per point instead of
+// about 64, and the last axis runs forward transform, eigenvalue division and
+// inverse in one launch: 2 d - 1 passes in all.
 #include <rocfft/rocfft.h>
 
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <vector>
 
 #include "../../include/gmg.h"
 #include "gmg_internal.h"
@@ -153,6 +162,283 @@ __global__ void __launch_bounds__(256) k_dst_unpack(const double2 *__restrict__ 
   }
 }
 
+
+// ---------------------------------------------------------------- axis kernel
+// DST-I along one axis, in place in LDS.  A pair of lines is the complex
+// sequence z_j = a_j + i b_j, j = 1 .. m; its odd extension of length N = 2^LOGN
+// = 2(m+1) is never formed: the first stage reads element j > N/2 as -z_{N-j}.
+// The FFT is Stockham's (natural order in and out) in radix-8 stages with a
+// radix-2 or radix-4 one at the end when 3 does not divide LOGN; N/8 threads
+// hold a pair's values in registers between stages and exchange them through
+// LDS.  A pair with N <= 512 lives in one wavefront and needs no barrier.  Only
+// the coefficients 1 .. m are formed by the last stage.
+//
+// A workgroup of T threads takes P = 8 T / N pairs: consecutive rows (ROWS,
+// the contiguous axis: every load and store is a run along x), or P adjacent
+// pairs of columns (x, x + 1), loaded and stored as runs of 16 P bytes of each
+// row of the strided axis.  EIG: forward transform, times scale / lambda, and
+// inverse transform of the same axis.
+//
+// Bound: memory, 16 B per point and pass (LDS moves 64 B per point, the FFT
+// takes about 50 operations).  A solve against rocFFT with pack and unpack
+// kernels (6 passes of about 64 B): 255^3 0.38 against 1.23 ms (66-74 us a
+// pass, 3.6-4.0 TB/s, 115 us the one with both transforms), 511^3 4.6 against
+// 9.3, 1023^3 42.5 against 78.8, 2D 4095^2 0.69 against 0.94 ms.
+// Padding: one element in 8 within a line (stage 1 writes runs of 8 per
+// thread), and lines 8 elements off a multiple of 16 (a strided tile's loads
+// write P lines at a time): both conflict-free.
+struct DstAxisArgs {
+  const double *src;
+  double *dst;        // may be src
+  const double2 *tw;  // exp(-2 pi i k / N), k = 0 .. N - 1
+  const double *eig;  // (4 / h^2) sin^2(k pi h / 2), k = 1 .. m
+  size_t stride;      // strided: elements between neighbours along the axis
+  size_t outer;       // strided: elements between consecutive outer indices
+  int m;
+  int pairs;          // pairs of lines: in all (ROWS), per outer index (strided)
+  int rows;           // ROWS: lines in all
+  int nblk, gsh;
+  int dim;
+  double scale;
+};
+
+// Threads of a workgroup.  LDS holds 8 pairs of N = 1024 per CU however they
+// are grouped, and a workgroup of several wavefronts per pair waits at its
+// barriers, so small workgroups overlap better: rows take 256 threads (or one
+// pair).  Strided tiles want long runs along x: 8 pairs (128 bytes) up to N =
+// 512, 4 and 2 pairs beyond (the runs of neighbouring workgroups share lines
+// in one XCD's L2).  1024 threads everywhere from N = 1024 on: 511^3 5.15
+// against 4.57 ms, 1023^3 49.1 against 42.5 ms, 2D 511^2 48 against 27 us.
+constexpr int dst_threads(int logn, bool rows) {
+  const int tp = (1 << logn) / 8;
+  if (rows) return tp > 256 ? tp : 256;
+  return logn >= 12 ? 1024 : logn >= 9 ? 512 : 256;
+}
+constexpr int dst_line(int logn) { return (1 << logn) + (1 << logn) / 8 + 8; }  // LDS elements
+constexpr size_t dst_lds(int logn, bool rows) {
+  return (size_t)(dst_threads(logn, rows) * 8 >> logn) * dst_line(logn) * sizeof(double2);
+}
+
+__device__ __forceinline__ double2 c_add(double2 a, double2 b) { return {a.x + b.x, a.y + b.y}; }
+__device__ __forceinline__ double2 c_sub(double2 a, double2 b) { return {a.x - b.x, a.y - b.y}; }
+__device__ __forceinline__ double2 c_mul(double2 a, double2 b) {
+  return {fma(a.x, b.x, -(a.y * b.y)), fma(a.x, b.y, a.y * b.x)};
+}
+__device__ __forceinline__ double2 c_mi(double2 a) { return {a.y, -a.x}; }  // times -i
+
+template <int R>
+__device__ __forceinline__ void c_fft(double2 *v) {
+  if constexpr (R == 2) {
+    const double2 t = v[1];
+    v[1] = c_sub(v[0], t);
+    v[0] = c_add(v[0], t);
+  } else if constexpr (R == 4) {
+    const double2 a = c_add(v[0], v[2]), b = c_sub(v[0], v[2]);
+    const double2 c = c_add(v[1], v[3]), d = c_mi(c_sub(v[1], v[3]));
+    v[0] = c_add(a, c);
+    v[1] = c_add(b, d);
+    v[2] = c_sub(a, c);
+    v[3] = c_sub(b, d);
+  } else {
+    double2 e[4] = {v[0], v[2], v[4], v[6]}, o[4] = {v[1], v[3], v[5], v[7]};
+    c_fft<4>(e);
+    c_fft<4>(o);
+    const double q = 0x1.6a09e667f3bcdp-1;  // sqrt(1/2)
+    o[1] = {q * (o[1].x + o[1].y), q * (o[1].y - o[1].x)};
+    o[2] = c_mi(o[2]);
+    o[3] = {q * (o[3].y - o[3].x), -(q * (o[3].x + o[3].y))};
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      v[k] = c_add(e[k], o[k]);
+      v[k + 4] = c_sub(e[k], o[k]);
+    }
+  }
+}
+
+template <int LOGN>
+struct DstLine {
+  static constexpr int N = 1 << LOGN, TP = N / 8;
+  static constexpr int RL = LOGN % 3 == 0 ? 8 : LOGN % 3 == 1 ? 2 : 4;  // last stage's radix
+  static __device__ __forceinline__ int pad(int i) { return i + (i >> 3); }
+  // the pair's threads have done their LDS accesses
+  static __device__ __forceinline__ void sync() {
+    if constexpr (TP <= 64)
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    else
+      __syncthreads();
+  }
+  // stage with radix 8 (not the last unless LOGN == 3)
+  template <int NS>
+  static __device__ __forceinline__ void twiddle8(double2 *v, int t, const GMG_GLOBAL double2 *tw) {
+    const int b = (t & (NS - 1)) * (N / (8 * NS));
+#pragma unroll
+    for (int k = 1; k < 8; ++k) v[k] = c_mul(v[k], double2{tw[k * b].x, tw[k * b].y});
+  }
+  template <int NS>
+  static __device__ __forceinline__ void stages(double2 *z, double2 *v, int t,
+                                                const GMG_GLOBAL double2 *tw) {
+    if constexpr (NS * 8 < N || (NS * 8 == N && RL == 8)) {
+      if constexpr (NS > 1) {
+        sync();
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = z[pad(t + k * TP)];
+        twiddle8<NS>(v, t, tw);
+      }
+      c_fft<8>(v);
+      if constexpr (NS * 8 == N) return;  // last: coefficient t + k N / 8 is v[k]
+      sync();
+      const int d = (t / NS) * (8 * NS) + (t & (NS - 1));
+#pragma unroll
+      for (int k = 0; k < 8; ++k) z[pad(d + k * NS)] = v[k];
+      stages<NS * 8>(z, v, t, tw);
+    } else {
+      // radix 2 or 4: 8 / RL butterflies b = t + h TP, coefficients b + k NS
+      sync();
+#pragma unroll
+      for (int h = 0; h < 8 / RL; ++h) {
+        const int b = t + h * TP;
+        double2 *w = v + h * RL;
+#pragma unroll
+        for (int k = 0; k < RL; ++k) {
+          w[k] = z[pad(b + k * NS)];
+          if (k > 0) w[k] = c_mul(w[k], double2{tw[k * b].x, tw[k * b].y});
+        }
+        c_fft<RL>(w);
+      }
+    }
+  }
+  // the sine coefficients of the pair staged at z (z_0 = z_{N/2} = 0): fn(k,
+  // a_k, b_k) for this thread's k in 1 .. m, twice the DST-I of each line
+  template <typename F>
+  static __device__ __forceinline__ void dst(double2 *z, int t, const GMG_GLOBAL double2 *tw, F fn) {
+    double2 v[8];
+    sync();
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const double2 x = z[pad(k < 4 ? t + k * TP : (8 - k) * TP - t)];
+      v[k] = k < 4 ? x : double2{-x.x, -x.y};
+    }
+    stages<1>(z, v, t, tw);
+    sync();
+#pragma unroll
+    for (int h = 0; h < 8 / RL; ++h)
+#pragma unroll
+      for (int k = 0; k < RL / 2; ++k) {
+        const int q = t + h * TP + k * (N / RL);
+        const double2 w = v[h * RL + k];
+        if (q > 0) fn(q, -w.y, w.x);
+      }
+  }
+};
+
+template <int LOGN, bool ROWS, bool EIG>
+__global__ void __launch_bounds__(dst_threads(LOGN, ROWS)) k_dst_axis(DstAxisArgs a) {
+  using L = DstLine<LOGN>;
+  constexpr int T = dst_threads(LOGN, ROWS), TP = L::TP, P = T / TP, LS = dst_line(LOGN);
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  double2 *sm = reinterpret_cast<double2 *>(smem_raw);
+  const int m = a.m, tid = threadIdx.x;
+  const int q = tid / TP, t = tid % TP;  // this thread's pair and place in it
+  double2 *z = sm + q * LS;
+  const GMG_GLOBAL double2 *tw = gbl(a.tw);
+  const int j = xcd_remap(blockIdx.x, a.nblk, a.gsh);
+  if (t == 0) z[0] = z[L::pad(m + 1)] = double2{0.0, 0.0};
+  if constexpr (ROWS) {
+    const int pr = j * P + q;
+    const bool ra = 2 * pr < a.rows, rb = 2 * pr + 1 < a.rows;
+    const GMG_GLOBAL double *pa = gbl(a.src) + (size_t)(2 * pr) * m, *pb = pa + m;
+    for (int i = t; i < m; i += TP) {
+      const double x = ra ? pa[i] : 0.0, y = rb ? pb[i] : 0.0;
+      z[L::pad(i + 1)] = double2{x, y};
+    }
+    GMG_GLOBAL double *da = gbl(a.dst) + (size_t)(2 * pr) * m, *db = da + m;
+    L::dst(z, t, tw, [&](int k, double x, double y) {
+      if (ra) da[k - 1] = x;
+      if (rb) db[k - 1] = y;
+    });
+  } else {
+    const int nb = (a.pairs + P - 1) / P;  // workgroups per outer index
+    const int o = j / nb, p0 = (j - o * nb) * P;
+    const int lp = tid % P, x = 2 * (p0 + lp);  // loads and stores: this thread's pair
+    const bool in0 = x < m, in1 = x + 1 < m;
+    const size_t off = (size_t)o * a.outer + x;
+    double2 *zl = sm + lp * LS;
+    for (int i = tid / P; i < m; i += TP) {
+      const GMG_GLOBAL double *s = gbl(a.src) + off + i * a.stride;
+      double2 v{0.0, 0.0};
+      if (in1)
+        v = {s[0], s[1]};
+      else if (in0)
+        v.x = s[0];
+      zl[L::pad(i + 1)] = v;
+    }
+    __syncthreads();
+    if constexpr (EIG) {
+      const GMG_GLOBAL double *e = gbl(a.eig);
+      const int xa = 2 * (p0 + q);
+      // (columns past the grid: any finite factor, they are zero)
+      const double lo = a.dim == 3 ? e[o + 1] : 0.0;
+      const double la = lo + e[min(xa + 1, m)], lb = lo + e[min(xa + 2, m)];
+      L::dst(z, t, tw, [&](int k, double re, double im) {
+        const double ek = e[k];
+        z[L::pad(k)] = double2{re * (a.scale / (la + ek)), im * (a.scale / (lb + ek))};
+      });
+      if (t == 0) z[0] = z[L::pad(m + 1)] = double2{0.0, 0.0};
+    }
+    L::dst(z, t, tw, [&](int k, double re, double im) { z[L::pad(k)] = double2{re, im}; });
+    __syncthreads();
+    for (int i = tid / P; i < m; i += TP) {
+      GMG_GLOBAL double *d = gbl(a.dst) + off + i * a.stride;
+      const double2 v = zl[L::pad(i + 1)];
+      if (in1) {
+        d[0] = v.x;
+        d[1] = v.y;
+      } else if (in0) {
+        d[0] = v.x;
+      }
+    }
+  }
+}
+
+template <int LOGN, bool ROWS, bool EIG>
+hipError_t run_axis(DstAxisArgs a, int outers, hipStream_t s) {
+  constexpr int T = dst_threads(LOGN, ROWS), P = T * 8 >> LOGN;
+  auto k = k_dst_axis<LOGN, ROWS, EIG>;
+  static int gsh = 0;
+  if (gsh == 0) {
+    hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)dst_lds(LOGN, ROWS));
+    if (e == hipSuccess) e = resident_shift((const void *)k, T, dst_lds(LOGN, ROWS), gsh);
+    if (e != hipSuccess) return e;
+  }
+  a.gsh = gsh;
+  a.nblk = outers * ((a.pairs + P - 1) / P);
+  gmg_launch(k, dim3(a.nblk), dim3(T), dst_lds(LOGN, ROWS), s, a);
+  return hipGetLastError();
+}
+
+// mode 0: rows, 1: strided, 2: strided with the eigenvalue division
+template <int LOGN>
+hipError_t run_axis_mode(int mode, const DstAxisArgs &a, int outers, hipStream_t s) {
+  return mode == 0   ? run_axis<LOGN, true, false>(a, 1, s)
+         : mode == 1 ? run_axis<LOGN, false, false>(a, outers, s)
+                     : run_axis<LOGN, false, true>(a, outers, s);
+}
+
+hipError_t launch_axis(int logn, int mode, const DstAxisArgs &a, int outers, hipStream_t s) {
+  switch (logn) {
+#define GMG_AXIS(L) case L: return run_axis_mode<L>(mode, a, outers, s);
+    GMG_AXIS(3) GMG_AXIS(4) GMG_AXIS(5) GMG_AXIS(6) GMG_AXIS(7) GMG_AXIS(8)
+    GMG_AXIS(9) GMG_AXIS(10) GMG_AXIS(11) GMG_AXIS(12) GMG_AXIS(13)
+#undef GMG_AXIS
+    default: return hipErrorInvalidValue;
+  }
+}
+
+// Whether the axis kernels run (dim, m): a pair's FFT of length 2(m+1) <= 8192
+// fits LDS with its padding (148 KB), and the radix-8 first stage needs 8.
+bool axis_ok(int m) { return m >= 3 && m <= 4095; }
+
 }  // namespace gmg
 
 using namespace gmg;
@@ -167,9 +453,20 @@ struct gmg_dst {
   size_t work_bytes = 0;
   rocfft_plan plan = nullptr;
   rocfft_execution_info info = nullptr;
+  // axis kernels: twiddles and eigenvalues, uploaded by the setup (the host
+  // copy stays until the plan goes)
+  bool axis = false;
+  double2 *tw = nullptr;
+  double *eig = nullptr;
+  std::vector<double> host;
 };
 
 namespace {
+
+#define HIPCHK_DST(x) \
+  do {                \
+    if ((x) != hipSuccess) return GMG_ERR_HIP; \
+  } while (0)
 
 constexpr size_t kAlignDst = 256;
 size_t up(size_t x) { return (x + kAlignDst - 1) / kAlignDst * kAlignDst; }
@@ -234,6 +531,81 @@ hipError_t dst_pass(gmg_dst *p, double *out, int eig, double scale) {
   return hipGetLastError();
 }
 
+// Set-up for the axis kernels: the tables in the workspace.
+gmg_status axis_setup(int dim, int m, void *workspace, size_t *ws_bytes, hipStream_t stream,
+                      gmg_dst **out) {
+  const int N = 2 * (m + 1);
+  const size_t ntw = 2 * (size_t)N, nd = ntw + (size_t)m + 1;
+  const size_t total = up(nd * sizeof(double));
+  if (!workspace) {
+    *ws_bytes = total;
+    return GMG_OK;
+  }
+  if (!out) return GMG_ERR_INVALID_ARG;
+  if (*ws_bytes < total || ((uintptr_t)workspace) % kAlignDst) return GMG_ERR_WORKSPACE;
+  gmg_dst *p = new gmg_dst();
+  p->axis = true;
+  p->dim = dim;
+  p->m = m;
+  p->stream = stream;
+  p->tw = (double2 *)workspace;
+  p->eig = (double *)workspace + ntw;
+  p->host.resize(nd);
+  const long double pi = 3.141592653589793238462643383279502884L;
+  for (int k = 0; k < N; ++k) {
+    p->host[2 * k] = (double)cosl(2 * pi * k / N);
+    p->host[2 * k + 1] = (double)-sinl(2 * pi * k / N);
+  }
+  const long double n2 = (long double)(m + 1) * (m + 1);
+  for (int k = 0; k <= m; ++k) {
+    const long double sv = sinl(pi * k / (2 * (m + 1)));
+    p->host[ntw + k] = (double)(4 * n2 * sv * sv);
+  }
+  if (hipMemcpyAsync(workspace, p->host.data(), nd * sizeof(double), hipMemcpyHostToDevice,
+                     stream) != hipSuccess) {
+    delete p;
+    return GMG_ERR_HIP;
+  }
+  *out = p;
+  return GMG_OK;
+}
+
+// x (f -> u), [y,] the last axis forward, divided by the eigenvalues and
+// back, [y,] x, all in place in u.
+gmg_status axis_solve(gmg_dst *p, double *u, const double *f) {
+  const int m = p->m, dim = p->dim;
+  int logn = 1;
+  while ((1 << logn) < 2 * (m + 1)) ++logn;
+  DstAxisArgs a{};
+  a.tw = p->tw;
+  a.eig = p->eig;
+  a.m = m;
+  a.dim = dim;
+  a.dst = u;
+  // every transform of a line comes out twice its DST-I; the inverse's scale
+  a.scale = std::pow(2.0 / double(m + 1), dim) * std::pow(0.25, dim);
+  auto rows = [&](const double *src) {
+    a.src = src;
+    a.rows = dim == 3 ? m * m : m;
+    a.pairs = (a.rows + 1) / 2;
+    return launch_axis(logn, 0, a, 1, p->stream);
+  };
+  // axis 1 (y) with outer z, or the last axis with outer y (2D: no outer)
+  auto strided = [&](int axis, int mode) {
+    a.src = u;
+    a.pairs = (m + 1) / 2;
+    a.stride = axis == 1 ? (size_t)m : (size_t)m * m;
+    a.outer = axis == 1 ? (size_t)m * m : (size_t)m;
+    return launch_axis(logn, mode, a, dim == 3 ? m : 1, p->stream);
+  };
+  HIPCHK_DST(rows(f));
+  if (dim == 3) HIPCHK_DST(strided(1, 1));
+  HIPCHK_DST(strided(dim - 1, 2));
+  if (dim == 3) HIPCHK_DST(strided(1, 1));
+  HIPCHK_DST(rows(u));
+  return GMG_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -243,6 +615,7 @@ gmg_status gmg_dst_setup(int dim, int levels, void *workspace, size_t *ws_bytes,
   if (!ws_bytes || (dim != 2 && dim != 3) || levels < 1) return GMG_ERR_INVALID_ARG;
   if (levels > (dim == 3 ? 10 : 14)) return GMG_ERR_INVALID_ARG;
   const int m = (1 << levels) - 1;
+  if (axis_ok(m)) return axis_setup(dim, m, workspace, ws_bytes, (hipStream_t)stream, out);
   if (!rocfft_ready()) return GMG_ERR_HIP;
   rocfft_plan plan = nullptr;
   if (make_plan(dim, m, &plan) != rocfft_status_success) return GMG_ERR_HIP;
@@ -292,6 +665,7 @@ gmg_status gmg_dst_setup(int dim, int levels, void *workspace, size_t *ws_bytes,
 
 gmg_status gmg_dst_solve(gmg_dst *p, double *u, const double *f) {
   if (!p || !u || !f || (const double *)u == f) return GMG_ERR_INVALID_ARG;
+  if (p->axis) return axis_solve(p, u, f);
   const double scale = std::pow(2.0 / double(p->m + 1), p->dim);
   const int m = p->m;
   const dim3 pgrid((m + 1 + 255) / 256, (unsigned)std::min<size_t>(dst_pairs(p->dim, m), 65535));
