@@ -476,7 +476,315 @@ __device__ __forceinline__ void bottom_body(const BottomArgs<T> &a, const GMG_GL
   });
 }
 
+
+// ---- Red-black V-cycle with a 2^DIM block of points per thread -------------
+// The bottom is a chain of dependent steps (11 per level for V(2,2)), so what
+// counts is the length of a step.  Every level gives thread b = (bx, by[, bz])
+// the 2 x 2 [x 2] points at storage indices 2 b .. 2 b + 1, with u and f in
+// registers for the whole sub-cycle:
+//  * half of a point's neighbours are the thread's own, the colour of a local
+//    point is a constant, and no index is computed inside a step;
+//  * LDS holds one array per local position (dx, dy[, dz]), so neighbouring
+//    threads read neighbouring elements, each with a row of zeros below index
+//    0; the pad points (storage index n - 1) are held at zero in registers;
+//  * the point (1, 1[, 1]) of block b is the fine centre 2 b + 1 of coarse point
+//    b, so a thread restricts to the coarse point of its own index, whose
+//    right-hand side goes straight to the coarse owner's slot;
+//  * the levels of at most 64 blocks (15^2, 7^3 and below) run in wavefront 0
+//    with no barrier.
+// Every expression is the one of the steps above in the same order (the first
+// colour of a zero start adds the zero sum of its neighbours).
+// 2D 63^2 .. 1 V(2,2): 23.8 -> 13.0 us, 3D 15^3 .. 1: 25.6 -> 16.9 us.
+template <int DIM, int K>
+struct BlkLv {
+  static constexpr int n = 1 << K, nb = n / 2, P = nb + 1;  // P: array pitch
+  static constexpr int SZ = DIM == 3 ? P * P * P : P * P;
+  static constexpr int NB = DIM == 3 ? nb * nb * nb : nb * nb;  // blocks (threads)
+  static constexpr int NP = 1 << DIM;
+  // first U array of level K (levels packed coarsest first)
+  static constexpr int off() {
+    if constexpr (K == 1)
+      return 0;
+    else
+      return BlkLv<DIM, K - 1>::off() + NP * BlkLv<DIM, K - 1>::SZ;
+  }
+  // U of levels 1 .. K, then the residual arrays of level K, then slack for
+  // the reads one past the last block
+  static constexpr int total() { return off() + NP * SZ + (NP - 1) * SZ + P * P + P + 2; }
+};
+
+struct BlkPar {
+  int nu1, nu2;
+  int c0;  // first colour of a post-smoothing sweep
+};
+
+template <typename T, int DIM, int K, bool WAVE>
+struct BlkCycle {
+  using Lv = BlkLv<DIM, K>;
+  static constexpr int NP = Lv::NP, P = Lv::P, SZ = Lv::SZ, nb = Lv::nb;
+  static constexpr int ST[3] = {1, P, P * P};
+
+  static __device__ __forceinline__ void sync() { Team<WAVE>::sync(); }
+  // block coordinates of this thread
+  static __device__ __forceinline__ int bc(int ax) {
+    return ((int)threadIdx.x >> (ax * (K - 1))) & (nb - 1);
+  }
+  static __device__ __forceinline__ int at() {
+    return ((DIM == 3 ? (bc(2) + 1) * P : 0) + bc(1) + 1) * P + bc(0) + 1;
+  }
+  // local point p is a pad of the last block along some axis
+  static __device__ __forceinline__ bool pad_point(int p) {
+    bool r = false;
+#pragma unroll
+    for (int ax = 0; ax < DIM; ++ax) r = r || (((p >> ax) & 1) && bc(ax) == nb - 1);
+    return r;
+  }
+  static __device__ __forceinline__ T nb_sum(const T *U, const T (&u)[NP], int p, int i) {
+    T nb = T(0);
+#pragma unroll
+    for (int ax = 0; ax < DIM; ++ax) {
+      const int o = p ^ (1 << ax);
+      const bool hi = (p >> ax) & 1;
+      const T lo_v = hi ? u[o] : U[o * SZ + i - ST[ax]];
+      const T hi_v = hi ? U[o * SZ + i + ST[ax]] : u[o];
+      nb = ax == 0 ? lo_v + hi_v : (nb + lo_v) + hi_v;
+    }
+    return nb;
+  }
+  // one half-sweep and its publication; ZERO: every neighbour is still zero
+  // (the colour is a template argument: chosen at run time it would index u
+  // dynamically, and u would live in scratch memory)
+  template <int COLOUR, bool ZERO>
+  static __device__ __forceinline__ void half(bool on, T *U, T (&u)[NP], const T (&f)[NP], int i,
+                                              T h2) {
+    if (on) {
+#pragma unroll
+      for (int p = 0; p < NP; ++p) {
+        if ((__builtin_popcount(p) + DIM + COLOUR) & 1) continue;
+        const T nb = ZERO ? T(0) : nb_sum(U, u, p, i);
+        const T v = point_solve<T, DIM>(h2, f[p], nb);
+        u[p] = pad_point(p) ? T(0) : v;
+        U[p * SZ + i] = u[p];
+      }
+    }
+    sync();
+  }
+
+  // V-cycle on levels K .. 1 from u (zero: u is zero and not published)
+  static __device__ __forceinline__ void run(const BlkPar a, T *sm, T *R, T (&u)[NP],
+                                             const T (&f)[NP]) {
+    const bool on = (int)threadIdx.x < Lv::NB;
+    T *U = sm + Lv::off();
+    const int i = at();
+    const T h = ldexp(T(1), -K), h2 = h * h, inv_h2 = T(Lv::n) * T(Lv::n);
+    // (threads beyond the level's blocks take part in the barriers only)
+#pragma unroll
+    for (int p = 0; p < NP; ++p) u[p] = T(0);
+    for (int s = 0; s < a.nu1; ++s) {
+      if (s == 0)
+        half<0, true>(on, U, u, f, i, h2);
+      else
+        half<0, false>(on, U, u, f, i, h2);
+      half<1, false>(on, U, u, f, i, h2);
+    }
+    if (a.nu1 == 0) {
+      if (on)
+#pragma unroll
+        for (int p = 0; p < NP; ++p) U[p * SZ + i] = T(0);
+      sync();
+    }
+    // residual of the own block; the neighbours below take its low sides
+    T r[NP];
+    if (on) {
+#pragma unroll
+      for (int p = 0; p < NP; ++p) {
+        r[p] = f[p] - (T(2 * DIM) * u[p] - nb_sum(U, u, p, i)) * inv_h2;
+        if (p != NP - 1) R[p * SZ + i] = r[p];
+      }
+    }
+    sync();
+    // full weighting to the coarse point of this block's index: the fine
+    // points 2 b .. 2 b + 2 along each axis, x first, then y, then z
+    T fc = T(0);
+    if (on) {
+      // at (gx, gy, gz) in 0 .. 2 from the block's corner
+      auto rv = [&](int gx, int gy, int gz) {
+        const int p = (gx & 1) | ((gy & 1) << 1) | ((gz & 1) << 2);
+        const int d = (gx >> 1) + (gy >> 1) * P + (gz >> 1) * P * P;
+        return d ? R[p * SZ + i + d] : r[p];
+      };
+      auto row = [&](int gy, int gz) {
+        return T(0.25) * rv(0, gy, gz) + T(0.5) * rv(1, gy, gz) + T(0.25) * rv(2, gy, gz);
+      };
+      auto plane = [&](int gz) {
+        return T(0.25) * row(0, gz) + T(0.5) * row(1, gz) + T(0.25) * row(2, gz);
+      };
+      fc = DIM == 3 ? T(0.25) * plane(0) + T(0.5) * plane(1) + T(0.25) * plane(2) : plane(0);
+    }
+    using C = BlkLv<DIM, K - 1>;
+    T *Uc = sm + C::off();
+    if constexpr (K == 2) {
+      // one-node level: 2d u / h^2 = f, in FP64
+      if (threadIdx.x == 0) {
+        const double hc = 0.5;
+        Uc[C::SZ - 1] = T((hc * hc * double(fc)) / double(2 * DIM));
+      }
+      sync();
+    } else {
+      // the right-hand side waits in the coarse owner's own slots of U
+      if (on) {
+        int p = 0, j = 0;
+#pragma unroll
+        for (int ax = DIM - 1; ax >= 0; --ax) {
+          p |= (bc(ax) & 1) << ax;
+          j = j * C::P + (bc(ax) >> 1) + 1;
+        }
+        Uc[p * C::SZ + j] = fc;
+      }
+      sync();
+      using Sub = BlkCycle<T, DIM, K - 1, (C::NB <= 64)>;
+      T uc[NP], fcb[NP];
+      if (!Sub::wave() || threadIdx.x < 64) {
+        const int j = Sub::at();
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+          fcb[p] = (int)threadIdx.x < C::NB ? Uc[p * C::SZ + j] : T(0);
+        Sub::run(a, sm, R, uc, fcb);
+      }
+      if constexpr (Sub::wave() && !WAVE) __syncthreads();
+    }
+    // interpolate and add: coarse points b - 1 and b along each axis
+    if (on) {
+      T v[2][2][2];
+#pragma unroll
+      for (int dz = 0; dz < (DIM == 3 ? 2 : 1); ++dz)
+#pragma unroll
+        for (int dy = 0; dy < 2; ++dy)
+#pragma unroll
+          for (int dx = 0; dx < 2; ++dx) {
+            const int cx = bc(0) - 1 + dx, cy = bc(1) - 1 + dy, cz = DIM == 3 ? bc(2) - 1 + dz : 0;
+            const int p = (cx & 1) | ((cy & 1) << 1) | (DIM == 3 ? (cz & 1) << 2 : 0);
+            const int j = ((DIM == 3 ? ((cz >> 1) + 1) * C::P : 0) + (cy >> 1) + 1) * C::P +
+                          (cx >> 1) + 1;
+            v[dz][dy][dx] = Uc[p * C::SZ + j];
+          }
+#pragma unroll
+      for (int p = 0; p < NP; ++p) {
+        auto xs = [&](int dz, int dy) {
+          return (p & 1) ? v[dz][dy][1] : T(0.5) * (v[dz][dy][0] + v[dz][dy][1]);
+        };
+        auto ys = [&](int dz) { return (p & 2) ? xs(dz, 1) : T(0.5) * (xs(dz, 0) + xs(dz, 1)); };
+        T e;
+        if (DIM == 3)
+          e = (p & 4) ? ys(1) : T(0.5) * (ys(0) + ys(1));
+        else
+          e = ys(0);
+        u[p] = pad_point(p) ? T(0) : u[p] + e;
+        U[p * SZ + i] = u[p];
+      }
+    }
+    sync();
+    if (a.c0 == 0) half<0, false>(on && a.nu2 > 0, U, u, f, i, h2);
+    for (int s = 0; s < a.nu2; ++s) {
+      half<1, false>(on, U, u, f, i, h2);
+      if (a.c0 == 1 || s + 1 < a.nu2) half<0, false>(on, U, u, f, i, h2);
+    }
+  }
+  static constexpr bool wave() { return WAVE; }
+};
+
+template <typename T, int DIM, int K>
+__device__ __forceinline__ void blk_bottom(const GMG_GLOBAL T *fin, GMG_GLOBAL T *uout,
+                                           const int *active, const BlkPar a, T *sm) {
+  using Lv = BlkLv<DIM, K>;
+  constexpr bool WAVE = Lv::NB <= 64;
+  using Cy = BlkCycle<T, DIM, K, WAVE>;
+  constexpr int m = Lv::n - 1;
+  const bool on = (int)threadIdx.x < Lv::NB;
+  auto point = [&](int p, int &g) {  // global index of local point p; false: none
+    const int x = 2 * Cy::bc(0) + (p & 1), y = 2 * Cy::bc(1) + ((p >> 1) & 1);
+    const int z = DIM == 3 ? 2 * Cy::bc(2) + (p >> 2) : 0;
+    g = (z * m + y) * m + x;
+    return on && x < m && y < m && z < m;
+  };
+  T f[Lv::NP], u[Lv::NP];
+#pragma unroll
+  for (int p = 0; p < Lv::NP; ++p) {
+    int g;
+    f[p] = point(p, g) ? fin[g] : T(0);
+  }
+  // (the right-hand side is on its way before the flag is read)
+  if (active && *gbl(active) == 0) return;
+  // zero rows below index 0 of every array, and the one-node level
+  for (int i = threadIdx.x; i < Lv::off() + Lv::NP * Lv::SZ; i += blockDim.x) sm[i] = T(0);
+  __syncthreads();
+  if (WAVE && threadIdx.x >= 64) return;  // (no barrier after this)
+  Cy::run(a, sm, sm + Lv::off() + Lv::NP * Lv::SZ, u, f);
+#pragma unroll
+  for (int p = 0; p < Lv::NP; ++p) {
+    int g;
+    if (point(p, g)) uout[g] = u[p];
+  }
+}
+
+constexpr int blk_threads(int dim, int L) {
+  return dim == 3 ? (L >= 4 ? 512 : 64) : (L >= 6 ? 1024 : L == 5 ? 256 : 64);
+}
+template <int DIM>
+size_t blk_lds(int L, size_t elem) {
+  int n = 1;
+  switch (L) {
+    case 2: n = BlkLv<DIM, 2>::total(); break;
+    case 3: n = BlkLv<DIM, 3>::total(); break;
+    case 4: n = BlkLv<DIM, 4>::total(); break;
+    case 5: n = BlkLv<DIM, 5>::total(); break;
+    case 6: n = BlkLv<DIM, 6>::total(); break;
+  }
+  return n * elem;
+}
+
 }  // namespace
+
+// One workgroup per problem (batch: one table entry each, of at most the
+// launch's level count).
+template <typename T, int DIM>
+__global__ void __launch_bounds__(DIM == 3 ? 512 : 1024) k_bottom_rb(BottomArgs<T> arg,
+                                                                     const BottomArgs<T> *tbl) {
+  const int *active = arg.active;
+  const T *fp = arg.f;
+  T *up = arg.u;
+  int L = arg.L;
+  BlkPar par{arg.nu1, arg.nu2, arg.post_forward ? 0 : 1};
+  if (tbl) {
+    const BottomArgs<T> *e = tbl + blockIdx.x;
+    active = e->active;
+    fp = e->f;
+    up = e->u;
+    L = e->L;
+    par = BlkPar{e->nu1, e->nu2, e->post_forward ? 0 : 1};
+  }
+  const GMG_GLOBAL T *fin = gbl(fp);
+  GMG_GLOBAL T *uout = gbl(up);
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  T *sm = reinterpret_cast<T *>(smem_raw);
+  switch (L) {
+    case 1:
+      if (threadIdx.x == 0 && !(active && *gbl(active) == 0)) {  // 2d u / h^2 = f, h = 1/2, FP64
+        const double h = 0.5;
+        uout[0] = T((h * h * double(fin[0])) / double(2 * DIM));
+      }
+      break;
+    case 2: blk_bottom<T, DIM, 2>(fin, uout, active, par, sm); break;
+    case 3: blk_bottom<T, DIM, 3>(fin, uout, active, par, sm); break;
+    case 4: blk_bottom<T, DIM, 4>(fin, uout, active, par, sm); break;
+    case 5:
+      if constexpr (DIM == 2) blk_bottom<T, DIM, 5>(fin, uout, active, par, sm);
+      break;
+    case 6:
+      if constexpr (DIM == 2) blk_bottom<T, DIM, 6>(fin, uout, active, par, sm);
+      break;
+  }
+}
 
 template <typename T>
 __global__ void __launch_bounds__(1024) k_bottom(BottomArgs<T> arg, const BottomArgs<T> *tbl) {
@@ -504,9 +812,29 @@ size_t bottom_lds_bytes(int dim, int L, int smoother, size_t elem) {
   return n_el * elem;
 }
 
+template <typename T, int DIM>
+hipError_t run_bottom_rb(int nproblems, BottomArgs<T> a, const BottomArgs<T> *tbl, hipStream_t s) {
+  static bool attr = false;
+  if (!attr) {
+    hipError_t e = hipFuncSetAttribute((const void *)k_bottom_rb<T, DIM>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)blk_lds<DIM>(DIM == 3 ? 4 : 6, sizeof(T)));
+    if (e != hipSuccess) return e;
+    attr = true;
+  }
+  gmg_launch((k_bottom_rb<T, DIM>), dim3(nproblems), dim3(blk_threads(DIM, a.L)),
+             blk_lds<DIM>(a.L, sizeof(T)), s, a, tbl);
+  return hipGetLastError();
+}
+
 template <typename T>
 hipError_t launch_bottom(int nproblems, BottomArgs<T> a, const BottomArgs<T> *tbl, hipStream_t s,
                          size_t lds_bytes) {
+  // red-black V-cycles: the block kernel, up to the sides it is built for (the
+  // one-workgroup levels never exceed them)
+  if (a.smoother == 0 && !a.fmg && a.L <= (a.dim == 3 ? 4 : 6))
+    return a.dim == 3 ? run_bottom_rb<T, 3>(nproblems, a, tbl, s)
+                      : run_bottom_rb<T, 2>(nproblems, a, tbl, s);
   const size_t lds = lds_bytes ? lds_bytes : bottom_lds_bytes(a.dim, a.L, a.smoother, sizeof(T));
   static bool attr = false;
   if (!attr) {

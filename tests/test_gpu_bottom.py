@@ -1,0 +1,40 @@
+"""The one-workgroup bottom kernel on every hierarchy it holds (2D 63^2 .. 1,
+3D 15^3 .. 1), with every sweep count down to zero on either side and both
+post-smoothing orders: V-cycles equal the oracle's to 1e-13 (the transfers' sums
+have another order: a few eps per level)."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import oracle  # noqa: E402
+from paper_1208_4247_amd import workloads as wl  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+def _vcycle(u, f, nu1, nu2, forward):
+    """The cycle from the oracle's pieces, with either post-smoothing order."""
+    if u.size == 1:
+        return f * 0.25 / (2 * u.ndim)
+    u = oracle.rbgs(u, f, nu1)
+    fc = oracle.restrict_fw(oracle.residual(u, f))
+    u = oracle.prolong_add(_vcycle(np.zeros_like(fc), fc, nu1, nu2, forward), u)
+    return oracle.rbgs(u, f, nu2, backward=not forward)
+
+
+@pytest.mark.parametrize("dim,L", [(2, L) for L in range(2, 8)] + [(3, L) for L in range(2, 6)])
+@pytest.mark.parametrize("nu", [(2, 2), (1, 1), (0, 2), (2, 0), (1, 3)])
+@pytest.mark.parametrize("forward", [False, True])
+def test_bottom_vcycle_matches_oracle(dim, L, nu, forward):
+    from paper_1208_4247_amd import capi
+    from paper_1208_4247_amd.solver import Plan
+
+    m = (1 << L) - 1
+    f = wl.rhs_uniform(dim, m, seed=500 + L)
+    fd = torch.from_numpy(f).cuda()
+    plan = Plan(dim, L, nu1=nu[0], nu2=nu[1], flags=capi.GMG_POST_FORWARD if forward else 0)
+    u = torch.zeros_like(fd)
+    plan.vcycle(u, fd)
+    want = _vcycle(np.zeros_like(f), f, nu[0], nu[1], forward)
+    assert np.linalg.norm(u.cpu().numpy() - want) <= 1e-13 * np.linalg.norm(want)
