@@ -1295,12 +1295,17 @@ gmg_status map_status(int s) {
   }
 }
 
-// Cycle bodies still needed judging from the contraction seen so far: the
-// state holds res_k after k = done cycles and cycle k+1 already ran.
+// Cycle bodies still needed judging from the contraction of the last cycle
+// (the mean since the start counts the first cycles, which contract smooth or
+// rough data otherwise than the rest: it enqueued 40 bodies for the 28 of a
+// 1023^3 V(1,1) solve and 19 for the 15 of a 255^3 V(2,2) one, where the last
+// cycle's gives 28 and 15): the state holds res_k after k = done cycles and
+// cycle k+1 already ran.
 int estimate_cycles(const SolveState &st, int done) {
   if (st.res0 <= 0.0 || st.res <= 0.0 || done <= 0) return 2;
   const double rel = st.res / st.res0;
-  const double rho = std::pow(rel, 1.0 / done);
+  const double rho = done >= 2 && st.res_prev > st.res ? st.res / st.res_prev
+                                                       : std::pow(rel, 1.0 / done);
   if (!(rho > 0.0) || rho >= 0.95) return 4;
   const double need = std::log(st.rtol / rel) / std::log(rho);
   int k = (int)std::ceil(need);
@@ -2565,7 +2570,9 @@ gmg_status gmg_solve(gmg_plan *p, double *u, const double *f, double rtol, int m
   const size_t N0 = npts(p->dim, m0);
   const double h = 1.0 / double(m0 + 1);
   int enq = 0;  // cycle bodies enqueued (body k checks the residual after k cycles)
-  int batch = 2;
+  // the first check needs two cycles behind it for a contraction (a refinement
+  // step holds several cycles and ends after a few: one)
+  int batch = std::min(mixed ? 2 : 3, maxit + 1);
   for (;;) {
     for (int b = 0; b < batch; ++b, ++enq) {
       p->prof_tag = enq;
@@ -2662,7 +2669,7 @@ gmg_status gmg_batch_solve(gmg_plan *p, double *const *u, const double *const *f
   HIPCHK(hipMemcpyAsync(b->dev_tbl, b->pinned, b->host_tbl.size(), hipMemcpyHostToDevice,
                         p->stream));
   HIPCHK(launch_state_init_batch(b->states, n, maxit, rtol, p->stream));
-  int enq = 0, batch = 2;
+  int enq = 0, batch = std::min(3, maxit + 1);
   for (;;) {
     for (int k = 0; k < batch; ++k, ++enq) HIPCHK(batch_run_cycle(p));
     HIPCHK(hipMemcpyAsync(b->hstates, b->states, sizeof(SolveState) * n, hipMemcpyDeviceToHost,

@@ -197,7 +197,7 @@ struct SolveState {
   double rtol;
   double res0;  // < 0: take from the first norm
   double res;   // last residual norm
-  double pad;
+  double res_prev;  // the one before it (0: none yet)
 };
 
 template <typename T>

@@ -32,6 +32,7 @@ __device__ __forceinline__ double sum_partials(const double *p, int n) {
 __device__ __forceinline__ void update_state(SolveState *st, double tot) {
   const double res = sqrt(tot);
   if (st->res0 < 0.0) st->res0 = res;
+  st->res_prev = st->res;
   st->res = res;
   const double res0 = st->res0;
   if (!isfinite(res)) {
@@ -504,7 +505,7 @@ __global__ void k_state_init_batch(SolveState *st, int n, int maxit, double rtol
     st[i].rtol = rtol;
     st[i].res0 = -1.0;
     st[i].res = 0.0;
-    st[i].pad = 0.0;
+    st[i].res_prev = 0.0;
   }
 }
 
@@ -522,7 +523,7 @@ __global__ void k_state_init(SolveState *st, int maxit, double rtol, double res0
     st->rtol = rtol;
     st->res0 = res0;
     st->res = 0.0;
-    st->pad = 0.0;
+    st->res_prev = 0.0;
   }
 }
 
