@@ -419,14 +419,16 @@ bool can_fuse_restrict(const gmg_plan *p, int level, int nsweeps, size_t elem) {
 // partials != NULL: the first pass emits |f - A src|^2 partial sums.
 // fc_out != NULL (pre-smoothing only): when the level allows it, the last
 // pass also writes the restricted residual f_c = R (f - A dst) to fc_out and
-// *fused is set; otherwise the caller restricts separately.
+// *fused is set; otherwise the caller restricts separately.  With ec and src
+// NULL the start value is P ec alone.
 template <typename T>
 hipError_t smooth_chain(gmg_plan *p, int level, int nsweeps, bool backward, const T *src,
                         const T *ec, const T *f, T *dst, T *tmp, double *partials,
                         const int *active, int cls, int *nparts, T *fc_out = nullptr,
                         bool *fused = nullptr) {
-  const int role = ec ? 1 : 0;
-  const bool fuse = fc_out && !ec && !backward && can_fuse_restrict(p, level, nsweeps, sizeof(T));
+  // (a descent from an interpolated start: full multigrid)
+  const int role = ec && !fc_out ? 1 : 0;
+  const bool fuse = fc_out && !backward && can_fuse_restrict(p, level, nsweeps, sizeof(T));
   if (fused) *fused = fuse;
   const int smax = p->ch[level][role].smax;
   const int dim = p->dim;
@@ -721,10 +723,12 @@ hipError_t run_coarse(gmg_plan *p, const int *active) {
 // u0_in (NULL = zero), result u0_out (must not alias u0_in), RHS f0.
 // norm_partials != NULL: the level-0 pre-pass emits the residual norm of
 // u0_in, and a finalize step updates the solve state right after it.
-// repeat: u0_in is the result of this plan's previous cycle on f0.
+// repeat: u0_in is the result of this plan's previous cycle on f0.  start_ec
+// (with u0_in NULL; L >= 2): the start value is P start_ec.
 template <typename T>
 hipError_t enqueue_vcycle(gmg_plan *p, const T *u0_in, const T *f0, T *u0_out,
-                          double *norm_partials, const int *active, bool repeat = false) {
+                          double *norm_partials, const int *active, bool repeat = false,
+                          const T *start_ec = nullptr) {
   LevelSet<T> &S = levels_of<T>(p);
   const int L = p->L;
   const bool bwd = !(p->cfg.flags & GMG_POST_FORWARD);
@@ -764,7 +768,7 @@ hipError_t enqueue_vcycle(gmg_plan *p, const T *u0_in, const T *f0, T *u0_out,
   if (repeat && p->carry && p->ch[0][0].smax >= 2)
     e = carry_pre<T>(p, u0_in, f0, S.w[0], S.t[0], norm_partials, active, S.f[1], &fused, &nparts);
   else
-    e = smooth_chain<T>(p, 0, nu1, false, u0_in, nullptr, f0, S.w[0], S.t[0], norm_partials,
+    e = smooth_chain<T>(p, 0, nu1, false, u0_in, start_ec, f0, S.w[0], S.t[0], norm_partials,
                         active, PC_PRE0, &nparts, S.f[1], &fused);
   if (e != hipSuccess) return e;
   // (nu1 == 0: the chain copied the start value into w0, so the post-pass
@@ -857,15 +861,15 @@ hipError_t enqueue_inner(gmg_plan *p, const int *active) {
 }
 
 // ------------------------------------------------------------------ FMG
-// One V-cycle on the levels s .. L-1 (1 <= s < B) from the start value in the
-// workspace u of level s, right-hand side f of level s, result back in u of
-// level s: the general passes on level s (non-zero start), then the usual
-// coarse part from level s+1.
+// One V-cycle on the levels s .. L-1 (1 <= s < B) from the start value P u_{s+1}
+// (full multigrid's; interpolated by the first pre-smoothing pass), right-hand
+// side f of level s, result in u of level s: the general passes on level s,
+// then the usual coarse part from level s+1.
 hipError_t enqueue_vcycle_level(gmg_plan *p, int s) {
   LevelSet<double> &S = p->d;
   const bool bwd = !(p->cfg.flags & GMG_POST_FORWARD);
   bool fused = false;
-  hipError_t e = smooth_chain<double>(p, s, p->cfg.nu1, false, S.u[s], nullptr, S.f[s], S.w[s],
+  hipError_t e = smooth_chain<double>(p, s, p->cfg.nu1, false, nullptr, S.u[s + 1], S.f[s], S.w[s],
                                       S.t[s], nullptr, nullptr, PC_PRE_C, nullptr, S.f[s + 1],
                                       &fused);
   if (e != hipSuccess) return e;
@@ -914,15 +918,10 @@ hipError_t enqueue_fmg(gmg_plan *p, double *u, const double *f) {
     if (e != hipSuccess) return e;
   }
   for (int l = B - 1; l >= 1; --l) {
-    e = launch_prolong_add<double>(p->dim, p->m[l], p->m[l + 1], nullptr, S.u[l + 1], S.u[l],
-                                   nullptr, p->stream);
-    if (e != hipSuccess) return e;
     e = enqueue_vcycle_level(p, l);
     if (e != hipSuccess) return e;
   }
-  e = launch_prolong_add<double>(p->dim, p->m[0], p->m[1], nullptr, S.u[1], u, nullptr, p->stream);
-  if (e != hipSuccess) return e;
-  return enqueue_vcycle<double>(p, u, f, u, nullptr, nullptr);
+  return enqueue_vcycle<double>(p, nullptr, f, u, nullptr, nullptr, false, S.u[1]);
 }
 
 // ------------------------------------------------------------------ paper variant

@@ -1192,7 +1192,12 @@ hipError_t run_wj(PassArgs<T> a, hipStream_t st, const PassArgs<T> *tbl, int nen
 #define GMG_RST_CASES_run_rb(RUN, T, D, S, E, Y, N)                                          \
   case F_RESTRICT: return RUN<T, D, S, E, Y, N, F_RESTRICT>(a, st, tbl, nent);              \
   case F_RESTRICT | F_ZERO_IN: return RUN<T, D, S, E, Y, N, F_RESTRICT | F_ZERO_IN>(a, st, tbl, nent); \
-  case F_RESTRICT | F_NORM_IN: return RUN<T, D, S, E, Y, N, F_RESTRICT | F_NORM_IN>(a, st, tbl, nent);
+  case F_RESTRICT | F_NORM_IN: return RUN<T, D, S, E, Y, N, F_RESTRICT | F_NORM_IN>(a, st, tbl, nent); \
+  case F_RESTRICT | F_ZERO_IN | F_PROLONG: /* full multigrid (FP64) */                        \
+    if constexpr (sizeof(T) == 8)                                                              \
+      return RUN<T, D, S, E, Y, N, F_RESTRICT | F_ZERO_IN | F_PROLONG>(a, st, tbl, nent);      \
+    else                                                                                       \
+      return hipErrorInvalidValue;
 #define GMG_RST_CASES_run_wj(RUN, T, D, S, E, Y, N)
 #define GMG_RST_CASES(RUN, T, D, S, E, Y, N) GMG_RST_CASES_##RUN(RUN, T, D, S, E, Y, N)
 #define GMG_FLAG_SWITCH(RUN, T, D, S, E, Y, N)                                            \
@@ -1201,6 +1206,11 @@ hipError_t run_wj(PassArgs<T> a, hipStream_t st, const PassArgs<T> *tbl, int nen
     case F_ZERO_IN: return RUN<T, D, S, E, Y, N, F_ZERO_IN>(a, st, tbl, nent);                    \
     case F_PROLONG: return RUN<T, D, S, E, Y, N, F_PROLONG>(a, st, tbl, nent);                    \
     case F_NORM_IN: return RUN<T, D, S, E, Y, N, F_NORM_IN>(a, st, tbl, nent);                    \
+    case F_ZERO_IN | F_PROLONG: /* full multigrid (FP64) */                                       \
+      if constexpr (sizeof(T) == 8)                                                               \
+        return RUN<T, D, S, E, Y, N, F_ZERO_IN | F_PROLONG>(a, st, tbl, nent);                    \
+      else                                                                                        \
+        return hipErrorInvalidValue;                                                              \
     case F_BLACK_FIRST: return RUN<T, D, S, E, Y, N, F_BLACK_FIRST>(a, st, tbl, nent);            \
     case F_ZERO_IN | F_BLACK_FIRST: return RUN<T, D, S, E, Y, N, F_ZERO_IN | F_BLACK_FIRST>(a, st, tbl, nent); \
     case F_PROLONG | F_BLACK_FIRST: return RUN<T, D, S, E, Y, N, F_PROLONG | F_BLACK_FIRST>(a, st, tbl, nent); \

@@ -105,8 +105,8 @@ __global__ void __launch_bounds__(NT) k_restrict(RestrictArgs<T> arg, const Rest
 
   // u-tile element q -> byte offset in its plane, out of range (kOOB) outside
   // the domain: loads go through one-plane buffer resources, so the zero
-  // boundary and a missing u (zero start) cost no branches and the next
-  // plane's loads stay in flight across the current plane's work
+  // boundary costs no branches and the next plane's loads stay in flight
+  // across the current plane's work
   int uo[NU];
 #pragma unroll
   for (int k = 0; k < NU; ++k) {
@@ -127,8 +127,7 @@ __global__ void __launch_bounds__(NT) k_restrict(RestrictArgs<T> arg, const Rest
     ro[k] = rin[k] ? (DIM == 3 ? y * m + x : x) * (int)sizeof(T) : kOOB;
   }
   auto load_u = [&](int z, T *v) {
-    // no u: a plane index outside the grid gives a resource with no records
-    const __amdgpu_buffer_rsrc_t r = plane_rsrc(a.u ? a.u : a.f, a.u ? z : -1, m, planeS);
+    const __amdgpu_buffer_rsrc_t r = plane_rsrc(a.u, z, m, planeS);
 #pragma unroll
     for (int k = 0; k < NU; ++k) v[k] = bload<T>(r, uo[k]);
   };
@@ -224,6 +223,62 @@ __global__ void __launch_bounds__(NT) k_restrict(RestrictArgs<T> arg, const Rest
 #pragma unroll
     for (int k = 0; k < NR; ++k) pf[k] = nf[k];
     __syncthreads();
+  }
+}
+
+// ------------------------------------------------------------------------
+// Full weighting of f itself (full multigrid's right-hand sides; the residual
+// of a zero iterate).  One thread per coarse column marches over a chunk of the
+// coarse axis: x from a pair load and the next lane's first value, y from three
+// rows, and the fine plane that two coarse planes share is kept, so every fine
+// plane is loaded once (its rows 1.5 times in 3D, from the caches).  Same sums
+// in the same order as k_restrict, whose LDS ring and barriers buy nothing
+// without an iterate.  Bound: HBM, 8 + 8 / 2^d B per fine point; 4095^2: 34 us
+// against 70 us.
+// ------------------------------------------------------------------------
+template <typename T, int DIM>
+__global__ void __launch_bounds__(256) k_restrict_f(const T *__restrict__ f, T *__restrict__ fc,
+                                                    const int *active, int m, int mc, int chunk) {
+  if (active && *gbl(active) == 0) return;
+  const int lane = threadIdx.x & 63;
+  const int cx = blockIdx.x * 64 + lane;
+  const int w = threadIdx.x >> 6;
+  const int cy = DIM == 3 ? blockIdx.y * 4 + w : 0;
+  const int part = DIM == 3 ? blockIdx.z : blockIdx.y * 4 + w;
+  const int C0 = part * chunk, C1 = min(C0 + chunk, mc);
+  const int planeS = DIM == 3 ? m * m : m;
+  // fine columns 2 cx, 2 cx + 1 (inside the grid for every coarse column), and
+  // 2 cx + 2 from the next lane (the last lane loads it)
+  const bool in = cx < mc && (DIM == 2 || cy < mc);
+  const int o0 = in ? ((DIM == 3 ? 2 * cy * m : 0) + 2 * cx) * (int)sizeof(T) : kOOB;
+  const bool own2 = lane == 63 || cx == mc - 1;
+  auto plane = [&](int z) {
+    const __amdgpu_buffer_rsrc_t r = plane_rsrc(f, z, m, planeS);
+    T s = T(0);
+    T row[DIM == 3 ? 3 : 1];
+#pragma unroll
+    for (int k = 0; k < (DIM == 3 ? 3 : 1); ++k) {
+      const int o = in ? o0 + k * m * (int)sizeof(T) : kOOB;
+      const PairOf<T> p = bload2<T>(r, o);
+      T c = __shfl_down(p.lo, 1);
+      if (own2) c = bload<T>(r, in ? o + 2 * (int)sizeof(T) : kOOB);
+      row[k] = T(0.25) * p.lo + T(0.5) * p.hi + T(0.25) * c;
+    }
+    if constexpr (DIM == 3)
+      s = T(0.25) * row[0] + T(0.5) * row[1] + T(0.25) * row[2];
+    else
+      s = row[0];
+    return s;
+  };
+  if (C0 >= C1) return;
+  T low = plane(2 * C0);
+  for (int c = C0; c < C1; ++c) {
+    const T mid = plane(2 * c + 1), high = plane(2 * c + 2);
+    T acc = T(0.25) * low;
+    acc += T(0.5) * mid;
+    acc += T(0.25) * high;
+    if (in) gbl(fc)[DIM == 3 ? ((size_t)c * mc + cy) * mc + cx : (size_t)c * mc + cx] = acc;
+    low = high;
   }
 }
 
@@ -606,9 +661,21 @@ __global__ void __launch_bounds__(256) k_axpy_f32(double *x, const float *__rest
 template <typename T>
 hipError_t launch_restrict(int dim, RestrictArgs<T> a, hipStream_t s, const RestrictArgs<T> *tbl,
                            int nent) {
+  const int mc = a.mc;
+  if (!a.u) {  // zero iterate: the right-hand side itself (no stop test, no table)
+    // chunks short enough that a few thousand wavefronts hide the latency
+    const int chunk = dim == 3 ? (mc >= 128 ? 8 : 2) : (mc >= 2047 ? 8 : mc >= 1023 ? 4 : 2);
+    const int parts = (mc + chunk - 1) / chunk;
+    if (dim == 3)
+      gmg_launch((k_restrict_f<T, 3>), dim3((mc + 63) / 64, (mc + 3) / 4, parts), dim3(256), 0, s,
+                 a.f, a.fc, a.active, a.m, mc, chunk);
+    else
+      gmg_launch((k_restrict_f<T, 2>), dim3((mc + 63) / 64, (parts + 3) / 4), dim3(256), 0, s, a.f,
+                 a.fc, a.active, a.m, mc, chunk);
+    return hipGetLastError();
+  }
   // tile and chunk by size: small coarse grids get small tiles and short
   // chunks (many short-lived workgroups), large ones long chunks
-  const int mc = a.mc;
   if (dim == 3) {
     if (mc >= 64) {
       const int ncx = (mc + 31) / 32, ncy = (mc + 7) / 8;
