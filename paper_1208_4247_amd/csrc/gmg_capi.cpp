@@ -44,17 +44,8 @@ size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 size_t npts(int dim, int m) { return dim == 3 ? (size_t)m * m * m : (size_t)m * m; }
 
-// largest side the one-workgroup bottom kernel holds in LDS
-int bottom_side_max(int dim, int smoother, size_t elem) {
-  for (int k = 7; k >= 1; --k) {
-    const int L = k;
-    if (bottom_lds_bytes(dim, L, smoother, elem) <= 150 * 1024) {
-      const int m = (1 << L) - 1;
-      return dim == 3 ? std::min(m, 15) : std::min(m, 63);
-    }
-  }
-  return 1;
-}
+// largest side the one-workgroup bottom kernel takes
+int bottom_side_max(int dim) { return (1 << bottom_max_levels(dim)) - 1; }
 
 struct Prof {
   std::string name;
@@ -107,7 +98,6 @@ struct BOp {
   size_t tbl_off = 0;
   int cls = 0;
   double bytes = 0.0;
-  size_t lds = 0;      // bottom: LDS bytes for the largest entry
   int bottom_L = 0;    // bottom: largest sub-hierarchy
   int bottom_dim = 3;
   int branch = 0;      // 0: the plan's stream; 1: the side stream (2D problems)
@@ -1256,8 +1246,7 @@ gmg_status init_plan_shape(gmg_plan &p, const gmg_config *cfg) {
   p.L = cfg->levels;
   p.m.resize(p.L);
   for (int l = 0; l < p.L; ++l) p.m[l] = (1 << (p.L - l)) - 1;
-  const size_t elem = cfg->precision == GMG_MIXED_FP32_IR ? sizeof(float) : sizeof(double);
-  const int mb = bottom_side_max(p.dim, cfg->smoother == GMG_SMOOTH_WJ ? 1 : 0, elem);
+  const int mb = bottom_side_max(p.dim);
   p.B = p.L;  // first level with side <= mb, but never level 0
   for (int l = 1; l < p.L; ++l)
     if (p.m[l] <= mb) {
@@ -1738,8 +1727,8 @@ struct BatchBuilder {
   void align_tbl() { b->host_tbl.resize(align_up(b->host_tbl.size())); }
 };
 
-int bottom_first_level(int dim, int L, int smoother) {
-  const int mb = bottom_side_max(dim, smoother, sizeof(double));
+int bottom_first_level(int dim, int L) {
+  const int mb = bottom_side_max(dim);
   for (int l = 1; l < L; ++l)
     if ((1 << (L - l)) - 1 <= mb) return l;
   return L - 1;
@@ -1916,7 +1905,7 @@ size_t batch_build(gmg_plan *p, Batch *b, int n, const int *dims, const int *lev
   const int sm = p->cfg.smoother == GMG_SMOOTH_WJ ? 1 : 0;
   b->shape_count.clear();
   for (int q = 0; q < n; ++q) {
-    const int B = bottom_first_level(dims[q], levels[q], sm);
+    const int B = bottom_first_level(dims[q], levels[q]);
     for (int l = 0; l < B; ++l) ++b->shape_count[{dims[q], (1 << (levels[q] - l)) - 1}];
   }
   b->pb.assign(n, BProblem());
@@ -1927,7 +1916,7 @@ size_t batch_build(gmg_plan *p, Batch *b, int n, const int *dims, const int *lev
     BProblem &pr = b->pb[q];
     pr.dim = dims[q];
     pr.L = levels[q];
-    pr.B = bottom_first_level(pr.dim, pr.L, sm);
+    pr.B = bottom_first_level(pr.dim, pr.L);
     pr.m.resize(pr.L);
     for (int l = 0; l < pr.L; ++l) pr.m[l] = (1 << (pr.L - l)) - 1;
     pr.st = b->states + q;
@@ -2055,12 +2044,8 @@ size_t batch_build(gmg_plan *p, Batch *b, int n, const int *dims, const int *lev
       a.post_forward = bwd ? 0 : 1;
       a.omega = wj_omega(p, pr.dim);
       bb.push(a);
-      const size_t lds = bottom_lds_bytes(pr.dim, a.L, sm, sizeof(double));
-      if (lds > op.lds) {
-        op.lds = lds;
-        op.bottom_L = a.L;
-        op.bottom_dim = pr.dim;
-      }
+      op.bottom_L = std::max(op.bottom_L, a.L);
+      op.bottom_dim = pr.dim;
     }
     if (op.nent > 0) b->ops.push_back(op);
   }
@@ -2140,7 +2125,7 @@ hipError_t batch_enqueue_cycle(gmg_plan *p) {
         a.dim = op.bottom_dim;
         a.L = op.bottom_L;
         a.smoother = p->cfg.smoother == GMG_SMOOTH_WJ ? 1 : 0;
-        e = launch_bottom<double>(op.nent, a, (const BottomArgs<double> *)tbl, s, op.lds);
+        e = launch_bottom<double>(op.nent, a, (const BottomArgs<double> *)tbl, s);
         break;
       }
     }

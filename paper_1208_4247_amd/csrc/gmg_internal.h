@@ -345,11 +345,11 @@ template <typename T>
 hipError_t launch_residual(int dim, ResidArgs<T> a, hipStream_t s);
 int residual_blocks(int dim, int m);
 // bottom: tbl != NULL gives one entry (problem) per workgroup; a.L must then
-// be the largest entry's level count (it sizes the LDS)
+// be the largest entry's level count (it sizes the workgroup and the LDS)
 template <typename T>
-hipError_t launch_bottom(int nproblems, BottomArgs<T> a, const BottomArgs<T> *tbl, hipStream_t s,
-                         size_t lds_bytes = 0);
-size_t bottom_lds_bytes(int dim, int L, int smoother, size_t elem);
+hipError_t launch_bottom(int nproblems, BottomArgs<T> a, const BottomArgs<T> *tbl, hipStream_t s);
+// most levels one workgroup runs: sides up to 15 (3D) and 63 (2D)
+constexpr int bottom_max_levels(int dim) { return dim == 3 ? 4 : 6; }
 hipError_t launch_ir_step(int dim, IrArgs a, hipStream_t s);
 bool small_level_ok(int dim, int m, int nsweeps, size_t elem);
 size_t small_lds_bytes(int dim, int nsweeps, size_t elem);

@@ -38,3 +38,25 @@ def test_bottom_vcycle_matches_oracle(dim, L, nu, forward):
     plan.vcycle(u, fd)
     want = _vcycle(np.zeros_like(f), f, nu[0], nu[1], forward)
     assert np.linalg.norm(u.cpu().numpy() - want) <= 1e-13 * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("dim,L", [(2, L) for L in range(2, 8)] + [(3, L) for L in range(2, 6)])
+@pytest.mark.parametrize("nu", [(2, 2), (1, 1), (0, 2), (3, 0)])
+@pytest.mark.parametrize("kind", ["wj", "fmg", "wj_fmg"])
+def test_bottom_jacobi_and_full_multigrid_match_oracle(dim, L, nu, kind):
+    from paper_1208_4247_amd.solver import Plan
+
+    m = (1 << L) - 1
+    f = wl.rhs_uniform(dim, m, seed=520 + L)
+    fd = torch.from_numpy(f).cuda()
+    wj = kind.startswith("wj")
+    plan = Plan(dim, L, nu1=nu[0], nu2=nu[1], smoother="wj" if wj else "rbgs")
+    kw = dict(smoother=oracle.WJ if wj else oracle.RBGS, omega=2 * dim / (2 * dim + 1))
+    u = torch.zeros_like(fd)
+    if kind == "wj":
+        plan.vcycle(u, fd)
+        want = oracle.vcycle(np.zeros_like(f), f, nu[0], nu[1], **kw)
+    else:
+        plan.fmg(u, fd)
+        want = oracle.fmg(f, nu[0], nu[1], **kw)
+    assert np.linalg.norm(u.cpu().numpy() - want) <= 1e-13 * np.linalg.norm(want)
