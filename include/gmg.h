@@ -92,8 +92,9 @@ typedef enum { GMG_F64 = 0, GMG_F32 = 1 } gmg_dtype;
                                        pre-smoothing pass (same results)      */
 /* The paper's own transfers and coarsest rule (with any smoother; FP64 single
  * problems only, GMG_ERR_UNSUPPORTED otherwise).  Such plans (and MCGS plans)
- * run one kernel per step and level, without the small-level kernels, the
- * bottom kernel or the folded restriction; GMG_USE_GRAPH and GMG_AUTOTUNE
+ * run one kernel per step and level, without the small-level kernels or the
+ * folded restriction, and with a bottom kernel (sides up to 15 in 3D, 63 in
+ * 2D) for MCGS with GMG_FE_TRANSFER alone; GMG_USE_GRAPH and GMG_AUTOTUNE
  * have no effect on them (red-black or Jacobi sweeps keep the default tile
  * choices). */
 #define GMG_FE_TRANSFER 0x80u       /* linear finite-element restriction and

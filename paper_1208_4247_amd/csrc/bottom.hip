@@ -462,4 +462,222 @@ template hipError_t launch_bottom<double>(int, BottomArgs<double>, const BottomA
 template hipError_t launch_bottom<float>(int, BottomArgs<float>, const BottomArgs<float> *,
                                          hipStream_t);
 
+// ------------------------------------------------------------------------
+// The bottom of the paper's own cycle (multicolour Gauss-Seidel, linear
+// finite-element transfers; variant.hip holds the kernels of the larger levels):
+// levels of side <= 15 (3D), <= 63 (2D) in one workgroup.  One launch per half
+// sweep and transfer cost 4 us each whatever the level, 27 us a level of V(1,1)
+// in 3D; a colour step here is one LDS round trip of a point per thread.  3D
+// 15^3 .. 1 V(1,1): 81 us by level, 15 us so (means over a solve).
+//
+// Node indices run 0 .. n, zero at both ends; thread b owns the nodes 2 b + o,
+// o in {0, 1}^d (one point per colour), with their right-hand sides in
+// registers, and restricts to and interpolates from the coarse node b.  All
+// sums are in the order of the per-level kernels: the same bits.
+// ------------------------------------------------------------------------
+namespace {
+
+struct VarPar {
+  int nu1, nu2, backward, relax;
+};
+
+template <int DIM, int K>
+struct VarCycle {
+  static constexpr int n = 1 << K, nb = n / 2, P = n + 1, PP = DIM == 3 ? P * P : 0;
+  static constexpr int SZ = DIM == 3 ? P * P * P : P * P;
+  static constexpr int NB = DIM == 3 ? nb * nb * nb : nb * nb;
+  static constexpr int NP = 1 << DIM;
+  static constexpr bool WAVE = NB <= 64;
+  static constexpr int PC = nb + 1, PPC = DIM == 3 ? PC * PC : 0;  // coarse pitches
+  // LDS: U of levels 1 .. K (coarsest first), then the residual, then the
+  // coarse right-hand side (both reused by every level)
+  static constexpr int off() {
+    if constexpr (K == 1) return 0;
+    else return VarCycle<DIM, K - 1>::off() + VarCycle<DIM, K - 1>::SZ;
+  }
+  static constexpr int total() { return off() + 2 * SZ + VarCycle<DIM, K - 1>::SZ; }
+
+  static __device__ __forceinline__ int bc(int d) {
+    return ((int)threadIdx.x / (d == 0 ? 1 : d == 1 ? nb : nb * nb)) % nb;
+  }
+  static __device__ __forceinline__ int node(int p) {  // LDS index of local point p
+    return (2 * (DIM == 3 ? bc(2) : 0) + (p >> 2)) * PP + (2 * bc(1) + ((p >> 1) & 1)) * P +
+           2 * bc(0) + (p & 1);
+  }
+  static __device__ __forceinline__ int coarse(int ox, int oy, int oz) {  // coarse node b + o
+    return (DIM == 3 ? bc(2) + oz : 0) * PPC + (bc(1) + oy) * PC + bc(0) + ox;
+  }
+  // bit p: local point p is an interior node
+  static __device__ __forceinline__ int interior() {
+    int v = 0;
+    if ((int)threadIdx.x >= NB) return 0;
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+      if ((bc(0) > 0 || (p & 1)) && (bc(1) > 0 || (p & 2)) && (DIM == 2 || bc(2) > 0 || (p & 4)))
+        v |= 1 << p;
+    return v;
+  }
+
+  template <bool BW>
+  static __device__ __forceinline__ void sweep(double *U, const double *f, int in) {
+    constexpr double h = 1.0 / n, h2 = h * h, diag = 2.0 * DIM;
+#pragma unroll
+    for (int s = 0; s < NP; ++s) {
+      const int c = BW ? NP - 1 - s : s;  // colour (i&1) + 2 (j&1) + 4 (k&1) = local point
+      if (in >> c & 1) {
+        const int q = node(c);
+        double r = h2 * f[c];
+        if (DIM == 3) r = r + (U[q - PP] + U[q + PP]);
+        U[q] = (r + ((U[q - 1] + U[q + 1]) + (U[q - P] + U[q + P]))) / diag;
+      }
+      Team<WAVE>::sync();
+    }
+  }
+  static __device__ __forceinline__ void smooth(double *U, const double *f, int in, int nsweeps,
+                                                int backward) {
+    for (int k = 0; k < nsweeps; ++k) {
+      if (backward)
+        sweep<true>(U, f, in);
+      else
+        sweep<false>(U, f, in);
+    }
+  }
+
+  // V-cycle on this level's U (start value in LDS); f: this thread's
+  // right-hand sides; sm, res, fcs: see the LDS map.  Ends synchronised.
+  static __device__ __forceinline__ void cycle(const VarPar a, double *sm, double *res,
+                                               double *fcs, const double *f) {
+    constexpr double inv_h2 = double(n) * n, diag = 2.0 * DIM;
+    double *const U = sm + off();
+    const int in = interior();
+    smooth(U, f, in, a.nu1, 0);
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+      if (in >> p & 1) {
+        const int q = node(p);
+        double nbs = U[q - 1] + U[q + 1] + U[q - P] + U[q + P];
+        if (DIM == 3) nbs = nbs + U[q - PP] + U[q + PP];
+        res[q] = f[p] - (diag * U[q] - nbs) * inv_h2;
+      }
+    Team<WAVE>::sync();
+    if (in & 1) {  // coarse node b is an interior node
+      const double *r = res + node(0);
+      const double mid = 2.0 * r[0] + (r[1] + r[-1]) + (r[P] + r[-P]) + (r[P + 1] + r[-P - 1]);
+      double s;
+      if (DIM == 3) {
+        const double *lo = r - PP, *hi = r + PP;
+        s = lo[0] + lo[-1] + lo[-P] + lo[-P - 1];
+        s = s + mid;
+        s = (s + (hi[0] + hi[1] + hi[P] + hi[P + 1])) * 0.0625;
+      } else {
+        s = mid * 0.125;
+      }
+      fcs[coarse(0, 0, 0)] = s;
+    }
+    Team<WAVE>::sync();
+    if constexpr (K == 2) {
+      if (threadIdx.x == 0) {  // one node, h = 1/2; a Gauss-Seidel sweep from zero is exact
+        const int one = DIM == 3 ? 13 : 4;
+        sm[one] = a.relax && a.nu1 == 0 ? 0.0 : (0.25 * fcs[one]) / diag;
+      }
+      Team<WAVE>::sync();
+    } else {
+      using Cc = VarCycle<DIM, K - 1>;
+      if (!Cc::WAVE || threadIdx.x < 64) {
+        double fc[NP];
+        const int inc = Cc::interior();
+#pragma unroll
+        for (int p = 0; p < NP; ++p) fc[p] = inc >> p & 1 ? fcs[Cc::node(p)] : 0.0;
+        Team<Cc::WAVE>::sync();
+        Cc::cycle(a, sm, res, fcs, fc);
+      }
+      if (!WAVE) __syncthreads();
+    }
+    const double *const E = sm + VarCycle<DIM, K - 1>::off();
+    if ((int)threadIdx.x < NB) {
+      const double c0 = E[coarse(0, 0, 0)];
+#pragma unroll
+      for (int p = 0; p < NP; ++p)
+        if (in >> p & 1)
+          U[node(p)] += p ? 0.5 * (c0 + E[coarse(p & 1, (p >> 1) & 1, p >> 2)]) : c0;
+    }
+    Team<WAVE>::sync();
+    smooth(U, f, in, a.nu2, a.backward);
+  }
+
+  static __device__ __forceinline__ void run(const double *uin, const double *fin, double *uout,
+                                             const int *active, const VarPar a, double *sm) {
+    constexpr int m = n - 1;
+    const int in = interior();
+    auto global = [&](int p) {  // storage index of local point p
+      const int x = 2 * bc(0) + (p & 1) - 1, y = 2 * bc(1) + ((p >> 1) & 1) - 1;
+      const int z = DIM == 3 ? 2 * bc(2) + (p >> 2) - 1 : 0;
+      return (z * m + y) * m + x;
+    };
+    double f[NP], u0[NP];
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      f[p] = in >> p & 1 ? gbl(fin)[global(p)] : 0.0;
+      u0[p] = uin && (in >> p & 1) ? gbl(uin)[global(p)] : 0.0;
+    }
+    if (active && *gbl(active) == 0) return;
+    for (int i = threadIdx.x; i < total(); i += blockDim.x) sm[i] = 0.0;
+    __syncthreads();
+    if (WAVE && threadIdx.x >= 64) return;  // (no barrier after this)
+    double *const U = sm + off();
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+      if (in >> p & 1) U[node(p)] = u0[p];
+    Team<WAVE>::sync();
+    cycle(a, sm, U + SZ, U + 2 * SZ, f);
+#pragma unroll
+    for (int p = 0; p < NP; ++p)
+      if (in >> p & 1) gbl(uout)[global(p)] = U[node(p)];
+  }
+};
+
+}  // namespace
+
+template <int DIM, int K>
+__global__ void __launch_bounds__(blk_threads(DIM, K)) k_var_bottom(const double *uin,
+                                                                    const double *f, double *uout,
+                                                                    const int *active, VarPar a) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  VarCycle<DIM, K>::run(uin, f, uout, active, a, reinterpret_cast<double *>(smem_raw));
+}
+
+template <int DIM, int K>
+static hipError_t run_var_bottom(const double *uin, const double *f, double *uout,
+                                 const int *active, VarPar a, hipStream_t s) {
+  constexpr size_t lds = VarCycle<DIM, K>::total() * sizeof(double);
+  auto k = k_var_bottom<DIM, K>;
+  hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                     (int)lds);
+  if (e != hipSuccess) return e;
+  gmg_launch(k, dim3(1), dim3(blk_threads(DIM, K)), lds, s, uin, f, uout, active, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_var_bottom(int dim, int levels, const double *uin, const double *f, double *uout,
+                             int nu1, int nu2, int backward, int relax, const int *active,
+                             hipStream_t s) {
+  const VarPar a{nu1, nu2, backward, relax};
+  if (dim == 3) {
+    switch (levels) {
+      case 2: return run_var_bottom<3, 2>(uin, f, uout, active, a, s);
+      case 3: return run_var_bottom<3, 3>(uin, f, uout, active, a, s);
+      case 4: return run_var_bottom<3, 4>(uin, f, uout, active, a, s);
+    }
+  } else if (dim == 2) {
+    switch (levels) {
+      case 2: return run_var_bottom<2, 2>(uin, f, uout, active, a, s);
+      case 3: return run_var_bottom<2, 3>(uin, f, uout, active, a, s);
+      case 4: return run_var_bottom<2, 4>(uin, f, uout, active, a, s);
+      case 5: return run_var_bottom<2, 5>(uin, f, uout, active, a, s);
+      case 6: return run_var_bottom<2, 6>(uin, f, uout, active, a, s);
+    }
+  }
+  return hipErrorInvalidValue;
+}
+
 }  // namespace gmg

@@ -390,6 +390,12 @@ hipError_t launch_prolong_fe(int dim, int m, int mc, const double *in, const dou
                              double *out, const int *active, hipStream_t s);
 hipError_t launch_coarsest(int dim, const double *f, double *u, int relax, int wj, int nsweeps,
                            double omega, const int *active, hipStream_t s);
+// the levels of side <= 2^levels - 1 of a V-cycle with that smoother and those
+// transfers in one workgroup (levels 2 .. bottom_max_levels; uin NULL = zero, may
+// equal uout)
+hipError_t launch_var_bottom(int dim, int levels, const double *uin, const double *f, double *uout,
+                             int nu1, int nu2, int backward, int relax, const int *active,
+                             hipStream_t s);
 hipError_t launch_fill_zero(void *dst, size_t bytes, hipStream_t s);
 
 }  // namespace gmg

@@ -60,3 +60,31 @@ def test_bottom_jacobi_and_full_multigrid_match_oracle(dim, L, nu, kind):
         plan.fmg(u, fd)
         want = oracle.fmg(f, nu[0], nu[1], **kw)
     assert np.linalg.norm(u.cpu().numpy() - want) <= 1e-13 * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("dim,L", [(2, L) for L in range(2, 9)] + [(3, L) for L in range(2, 7)])
+@pytest.mark.parametrize("nu", [(1, 1), (0, 2), (3, 0), (2, 3)])
+@pytest.mark.parametrize("flags", [0, 0x8 | 0x100])  # GMG_POST_FORWARD, GMG_COARSE_RELAX
+def test_paper_bottom_same_bits_as_kernel_per_step(dim, L, nu, flags):
+    from paper_1208_4247_amd import capi
+    from paper_1208_4247_amd.solver import Plan
+
+    m = (1 << L) - 1
+    f = wl.rhs_uniform(dim, m, seed=560 + L)
+    u0 = wl.rhs_uniform(dim, m, seed=580 + L)
+    out = []
+    for extra in (0, capi.GMG_NO_FUSED_COARSE):
+        plan = Plan(dim, L, nu1=nu[0], nu2=nu[1], smoother="mcgs",
+                    flags=flags | capi.GMG_FE_TRANSFER | extra)
+        fd = torch.from_numpy(f).cuda()
+        u = torch.from_numpy(u0).cuda()
+        plan.vcycle(u, fd)
+        v = torch.zeros_like(u)
+        plan.fmg(v, fd)
+        out.append((u.cpu().numpy(), v.cpu().numpy()))
+    assert np.array_equal(out[0][0], out[1][0])
+    assert np.array_equal(out[0][1], out[1][1])
+    if not flags:
+        kw = dict(smoother=oracle.MCGS, variant=oracle.FE_TRANSFER)
+        want = oracle.vcycle(u0, f, nu[0], nu[1], **kw)
+        assert np.linalg.norm(out[0][0] - want) <= 1e-13 * np.linalg.norm(want)
