@@ -272,8 +272,9 @@ gmg_status gmg_plan_get_tile(const gmg_plan *p, int level, int role, int *stages
 gmg_status gmg_tune_cache_check(const char *path, int *n_valid, int *n_invalid);
 
 /* ---------------------------------------------------------------------- */
-/* Operator primitives.  Each runs exactly the kernels the cycle runs for  */
-/* one step, on problem 0's level `level` (side m = gmg_level_side(p,0,l)).*/
+/* Operator primitives.  Each runs the kernels the cycle runs for one step */
+/* (or, where the cycle does several in one kernel, kernels of the same    */
+/* bits), on problem 0's level `level` (side m = gmg_level_side(p,0,l)).   */
 /* Pointers: device arrays of m^d (fine) or mc^d (coarse, mc = (m-1)/2)    */
 /* elements of dtype dt.  Enqueue only unless a host output is requested. */
 /* ---------------------------------------------------------------------- */

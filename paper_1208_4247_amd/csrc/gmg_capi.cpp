@@ -917,9 +917,11 @@ hipError_t enqueue_fmg(gmg_plan *p, double *u, const double *f) {
 // ------------------------------------------------------------------ paper variant
 // nsweeps of the plan's smoother on level l from src (NULL = zero) into dst,
 // alternating with tmp so that the last sweep lands in dst and no launch
-// reads what it writes.  Red-black and Jacobi reuse the plain passes.
+// reads what it writes.  Red-black and Jacobi reuse the plain passes.  ec
+// (multicolour Gauss-Seidel, nsweeps >= 1): from src + P ec, finite elements.
 hipError_t var_smooth(gmg_plan *p, int l, int nsweeps, bool backward, const double *src,
-                      const double *f, double *dst, double *tmp, const int *active, int cls) {
+                      const double *f, double *dst, double *tmp, const int *active, int cls,
+                      const double *ec = nullptr) {
   if (p->cfg.smoother != GMG_SMOOTH_MCGS)
     return smooth_chain<double>(p, l, nsweeps, backward, src, nullptr, f, dst, tmp, nullptr,
                                 active, cls, nullptr);
@@ -939,9 +941,12 @@ hipError_t var_smooth(gmg_plan *p, int l, int nsweeps, bool backward, const doub
     for (int part = 0; part < parts; ++part) {
       // algorithmic bytes of a sweep: old values and f read, result written
       // once (3D: half of them in each part)
-      ProfScope ps(p, cls, (double)bytes * 3.0 / parts);
+      // (and of the interpolated values)
+      const double *e_in = k == 1 ? ec : nullptr;
+      ProfScope ps(p, cls, (double)bytes * 3.0 / parts +
+                               (e_in ? (double)npts(p->dim, (m - 1) / 2) * sizeof(double) : 0.0));
       hipError_t e = launch_mc_sweep(p->dim, m, in, f, out, backward ? 1 : 0, h * h, active,
-                                     p->stream, part);
+                                     p->stream, part, e_in);
       if (e != hipSuccess) return e;
     }
     in = out;
@@ -1039,10 +1044,15 @@ hipError_t var_cycle(gmg_plan *p, int s, const double *u_in, const double *f_s, 
   if (e != hipSuccess) return e;
   for (int l = b - 1; l >= s; --l) {
     const double *f = l == s ? f_s : S.f[l];
-    e = var_prolong(p, l, S.w[l], S.u[l + 1], S.w[l], active);
-    if (e != hipSuccess) return e;
+    // the paper's own sweep interpolates as it reads: no pass of its own
+    const bool pro = nu2 >= 1 && p->cfg.smoother == GMG_SMOOTH_MCGS &&
+                     (p->cfg.flags & GMG_FE_TRANSFER);
+    if (!pro) {
+      e = var_prolong(p, l, S.w[l], S.u[l + 1], S.w[l], active);
+      if (e != hipSuccess) return e;
+    }
     e = var_smooth(p, l, nu2, bwd, S.w[l], f, l == s ? u_out : S.u[l], S.t[l], active,
-                   l == 0 ? PC_POST0 : PC_POST_C);
+                   l == 0 ? PC_POST0 : PC_POST_C, pro ? S.u[l + 1] : nullptr);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

@@ -39,6 +39,17 @@ namespace gmg {
 // Work is organised by 2x2 quads (one point of each colour) aligned to even
 // storage indices; thread t owns quads t, t + NT, ...  Every launch reads src
 // (and, in 3D, zsrc) and writes dst; no launch reads what it writes.
+//
+// PRO: the sweep starts from src + P ec, the linear finite-element
+// interpolation (eq. Prolongation2d and its 3D analogue; k_prolong_fe below)
+// added as the values are read: 1 to src and zsrc (the first launch), 2 to src
+// alone (3D's second, whose zsrc the first has written).  With q the quad's
+// index its points lie between the coarse nodes (q, r), (q+1, r), (q, r+1) and
+// (q+1, r+1) = E[0..3] of one coarse plane: a point of a plane of even node
+// index gets the mean of its E[k] and E[3], one of an odd plane that of E[k] and
+// the next coarse plane's E[3].  Bound by memory traffic: interpolating in a
+// pass of its own took 60 to 69 us of a 255^3 cycle and the sweep's two launches
+// 51 us each after it; 59 us each so (127^3: 10 + 2 x 13.3 us, 2 x 11.5 us so).
 // ------------------------------------------------------------------------
 struct McArgs {
   const double *src;   // old values of the planes being updated (NULL: zero)
@@ -52,6 +63,8 @@ struct McArgs {
   int ntx, nty;  // tiles along x, y
   int czp;       // 3D: own planes per workgroup
   double h2;
+  const double *ec;  // PRO: coarse values, side mc
+  int mc;
 };
 
 // Raw buffer over the part of an array a tile reads: in 3D one plane (no
@@ -70,7 +83,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t mc_rsrc(const double *base, in
                                            n * (int)sizeof(double), 0x00020000);
 }
 
-template <int DIM, int QX, int QY, int NT>
+template <int DIM, int QX, int QY, int NT, int PRO>
 __global__ void __launch_bounds__(NT) k_mc_sweep(McArgs a) {
   if (a.active && *a.active == 0) return;
   constexpr int W = 2 * QX, H = 2 * QY;  // D2 extent
@@ -119,6 +132,32 @@ __global__ void __launch_bounds__(NT) k_mc_sweep(McArgs a) {
       }
   }
 
+  // PRO: E of coarse plane (node index of the plane) / 2, that of the coarse
+  // plane above, and the byte offsets of a quad's four coarse nodes
+  double ca[QPT][4], cn[QPT][4];
+  int oc[QPT][4];
+  auto coarse = [&](int kc, double (*E)[4]) {  // coarse plane of node index kc
+    int cyb = 0;
+    const __amdgpu_buffer_rsrc_t rc = mc_rsrc(a.ec, DIM, kc - 1, a.mc, yb / 2 - 1, H / 2 + 1, &cyb);
+#pragma unroll
+    for (int i = 0; i < QPT; ++i)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) E[i][k] = bload<double>(rc, oc[i][k]);
+  };
+  if (PRO) {
+    int cyb = 0;
+    (void)mc_rsrc(a.ec, DIM, 0, a.mc, yb / 2 - 1, H / 2 + 1, &cyb);
+#pragma unroll
+    for (int i = 0; i < QPT; ++i)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int x = (xb + lx0[i]) / 2 - 1 + (k & 1), y = (yb + ly0[i]) / 2 - 1 + (k >> 1);
+        const bool in = x >= 0 && x < a.mc && y >= 0 && y < a.mc;
+        oc[i][k] = in ? ((y - cyb) * a.mc + x) * (int)sizeof(double) : kOOB;
+      }
+    coarse((z_first + 1) / 2, ca);
+  }
+
   double R[QPT][4];    // h^2 f + z-neighbours of the quad's points
   double zlo[QPT][4];  // 3D: the plane below, carried from one own plane to the next
   if (DIM == 3) {
@@ -128,6 +167,14 @@ __global__ void __launch_bounds__(NT) k_mc_sweep(McArgs a) {
     for (int i = 0; i < QPT; ++i)
 #pragma unroll
       for (int k = 0; k < 4; ++k) zlo[i][k] = bload<double>(rz, off[i][k]);
+    if (PRO == 1) {
+      double cm[QPT][4];
+      coarse((z_first + 1) / 2 - (a.pz ? 0 : 1), cm);
+#pragma unroll
+      for (int i = 0; i < QPT; ++i)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) zlo[i][k] = zlo[i][k] + 0.5 * (cm[i][k] + ca[i][3]);
+    }
   }
 
   // loads of one own plane: old values, f and (3D) the plane above; issued
@@ -148,6 +195,7 @@ __global__ void __launch_bounds__(NT) k_mc_sweep(McArgs a) {
         pf[i][k] = bload<double>(rf, off[i][k]);
         if (DIM == 3) pz[i][k] = bload<double>(rzh, off[i][k]);
       }
+    if (PRO && DIM == 3) coarse((z + 1) / 2 + 1, cn);
   };
   load_plane(z_first);
 
@@ -158,6 +206,11 @@ __global__ void __launch_bounds__(NT) k_mc_sweep(McArgs a) {
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         double r = a.h2 * pf[i][k];
+        if (PRO) {
+          pu[i][k] = pu[i][k] + 0.5 * (ca[i][k] + (DIM == 3 && a.pz ? cn[i][3] : ca[i][3]));
+          if (DIM == 3 && PRO == 1)
+            pz[i][k] = pz[i][k] + 0.5 * ((a.pz ? cn[i][k] : ca[i][k]) + cn[i][3]);
+        }
         if (DIM == 3) {
           r = r + (zlo[i][k] + pz[i][k]);
           zlo[i][k] = pz[i][k];  // the plane above is the next own plane's plane below
@@ -165,6 +218,12 @@ __global__ void __launch_bounds__(NT) k_mc_sweep(McArgs a) {
         R[i][k] = r;
         U[(ly0[i] + (k >> 1)) * W + lx0[i] + (k & 1)] = pu[i][k];
       }
+    if (PRO && DIM == 3) {
+#pragma unroll
+      for (int i = 0; i < QPT; ++i)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) ca[i][k] = cn[i][k];
+    }
     if (o + 1 < nown) load_plane(z + 2);
     __syncthreads();
     // four colour steps on D1 (the tile plus a halo of one point)
@@ -429,7 +488,7 @@ __global__ void k_coarsest(const double *f, double *u, int dim, int relax, int w
 // launchers
 // ------------------------------------------------------------------------
 namespace {
-template <int DIM, int QX, int QY, int NT>
+template <int DIM, int QX, int QY, int NT, int PRO>
 hipError_t mc_launch(McArgs a, hipStream_t s) {
   constexpr int TX = 2 * QX - 4, TY = 2 * QY - 4;
   const int m = a.m;
@@ -445,21 +504,24 @@ hipError_t mc_launch(McArgs a, hipStream_t s) {
     a.czp = std::max(2, std::min(16, own * tiles / 2048));
     nz = (own + a.czp - 1) / a.czp;
   }
-  gmg_launch((k_mc_sweep<DIM, QX, QY, NT>), dim3(tiles, nz), dim3(NT), 0, s, a);
+  gmg_launch((k_mc_sweep<DIM, QX, QY, NT, PRO>), dim3(tiles, nz), dim3(NT), 0, s, a);
   return hipGetLastError();
 }
 
-template <int DIM>
+template <int DIM, int PRO>
 hipError_t mc_sweep_dim(McArgs a, hipStream_t s) {
-  if (a.m >= (DIM == 3 ? 127 : 255))
-    return DIM == 3 ? mc_launch<DIM, 64, 16, 512>(a, s) : mc_launch<DIM, 64, 16, 256>(a, s);
-  return mc_launch<DIM, 16, 8, 128>(a, s);
+  if (a.m < (DIM == 3 ? 127 : 255)) return mc_launch<DIM, 16, 8, 128, PRO>(a, s);
+  // 3D: one quad per thread (60 x 28 tile) keeps 62 registers, 94 with the
+  // coarse values; two (124 x 28, 125 registers) took 51.3 against 50.4 us a
+  // launch at 255^3 and 13.3 against 9.5 us at 127^3
+  return mc_launch<DIM, DIM == 3 ? 32 : 64, 16, DIM == 3 ? 512 : 256, PRO>(a, s);
 }
 }  // namespace
 
 hipError_t launch_mc_sweep(int dim, int m, const double *src, const double *f, double *dst,
-                           int backward, double h2, const int *active, hipStream_t s, int part) {
-  if (m < 1 || !f || !dst || dst == src || dst == f) return hipErrorInvalidValue;
+                           int backward, double h2, const int *active, hipStream_t s, int part,
+                           const double *ec) {
+  if (m < 1 || (ec && !src) || !f || !dst || dst == src || dst == f) return hipErrorInvalidValue;
   McArgs a{};
   a.src = src;
   a.f = f;
@@ -468,7 +530,9 @@ hipError_t launch_mc_sweep(int dim, int m, const double *src, const double *f, d
   a.m = m;
   a.backward = backward;
   a.h2 = h2;
-  if (dim == 2) return mc_sweep_dim<2>(a, s);
+  a.ec = ec;
+  a.mc = (m - 1) / 2;
+  if (dim == 2) return ec ? mc_sweep_dim<2, 1>(a, s) : mc_sweep_dim<2, 0>(a, s);
   // forward: planes of even node index, then odd; backward: odd, then even
   const int first = backward ? 1 : 0;
   if (part == 0) {
@@ -478,7 +542,8 @@ hipError_t launch_mc_sweep(int dim, int m, const double *src, const double *f, d
     a.pz = 1 - first;
     a.zsrc = dst;  // the planes the first part updated
   }
-  return mc_sweep_dim<3>(a, s);
+  if (!ec) return mc_sweep_dim<3, 0>(a, s);
+  return part == 0 ? mc_sweep_dim<3, 1>(a, s) : mc_sweep_dim<3, 2>(a, s);
 }
 
 hipError_t launch_restrict_fe(int dim, int m, int mc, const double *u, const double *f, double *fc,
