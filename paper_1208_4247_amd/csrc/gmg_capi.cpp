@@ -388,19 +388,23 @@ int last_pass_sweeps(int nu, int smax, int *npasses) {
 }
 
 // Whether the pre-smoothing of `level` (nsweeps sweeps in passes of the
-// level's pre choice) can end in a pass that also restricts: red-black, a
+// level's pre choice) can end in a pass that also restricts: a
 // coarser level exists, the choice asks for it, and the last pass's tile
 // fits in LDS with the restriction's planes.
 bool can_fuse_restrict(const gmg_plan *p, int level, int nsweeps, size_t elem) {
-  if (p->cfg.smoother != GMG_SMOOTH_RBGS || (p->cfg.flags & GMG_NO_FUSED_RESTRICT)) return false;
-  if (nsweeps < 1 || level + 1 >= p->L) return false;
+  const bool wj = p->cfg.smoother == GMG_SMOOTH_WJ;
+  if ((!wj && p->cfg.smoother != GMG_SMOOTH_RBGS) || (p->cfg.flags & GMG_NO_FUSED_RESTRICT))
+    return false;
+  if (nsweeps < 1 || level + 1 >= p->L || is_variant(p)) return false;
   const PassChoice &c = p->ch[level][0];
   if (!c.fuse) return false;
   const int st = stages_of(p, last_pass_sweeps(nsweeps, c.smax, nullptr));
-  if (pass_geometry(p->dim, p->m[level], st, pass_variant(p->dim, st, 0, c.var[st]), c.tz[st], true)
+  if (wj && !wj_pass_folds(p->dim, st, c.var[st], elem)) return false;
+  if (pass_geometry(p->dim, p->m[level], st, pass_variant(p->dim, st, wj ? 1 : 0, c.var[st]),
+                    c.tz[st], true)
           .nblocks > kMaxPartials)
     return false;
-  return rb_pass_fits(p->dim, st, c.var[st], F_RESTRICT | F_NORM_IN, elem);
+  return wj || rb_pass_fits(p->dim, st, c.var[st], F_RESTRICT | F_NORM_IN, elem);
 }
 
 // nsweeps of the plan's smoother from (src [+ P ec]) to dst through fused
@@ -1188,13 +1192,18 @@ int auto_tz(int dim, int m, int st, const PassTile &t) {
 //    three-stage pass 126 against 90 + 60 us; at 127^3 the tuner keeps the
 //    two, 35 us together); not into the four-stage FP64 pass, which has no
 //    registers left for it (the tuner never folds it, 1266 us at 511^3).
+//    Jacobi's two-sweep pass: from side 255 up (V(2,2) cycle 511^3 1866 against
+//    2326 us, 255^3 326 against 348, 127^3 113 both ways; 4095^2 348 against
+//    416, 511^2 65 against 71, 255^2 47 both ways).
 PassChoice choice_for(const gmg_config &cfg, int dim, int m, int role, int smax_cap) {
   PassChoice c;
   const bool wj = cfg.smoother == GMG_SMOOTH_WJ;
   const bool fp32 = cfg.precision == GMG_MIXED_FP32_IR;
   const bool may_fold = !wj && !(cfg.flags & GMG_NO_FUSED_RESTRICT);
   c.smax = smax_cap;
-  if (dim == 3)
+  if (wj)
+    c.fuse = m >= 255;
+  else if (dim == 3)
     c.fuse = role == 2 ? m >= 255 : (cfg.nu1 == 1 ? m >= 255 : fp32 && m >= 511);
   else
     c.fuse = fp32 || m >= (role == 0 && cfg.nu1 == 1 ? 127 : 255);
@@ -1208,7 +1217,8 @@ PassChoice choice_for(const gmg_config &cfg, int dim, int m, int role, int smax_
       tz = m <= 15 ? 2 : m <= 31 ? 3 : m <= 63 ? 4 : m <= 127 ? 8 : m <= 255 ? 64 : m <= 511 ? 256 : 341;
       if (wj) {
         v = m <= 63 ? 2 : m <= 127 || (st == 1 && m >= 511) ? 1 : 0;
-        if (m >= 255) tz = m <= 255 ? 43 : st == 1 ? 86 : 171;
+        const bool fold = c.fuse && st == 2 && role == 0 && !(cfg.flags & GMG_NO_FUSED_RESTRICT);
+        if (m >= 255) tz = m <= 255 ? (fold ? 64 : 43) : st == 1 ? 86 : 171;
       } else if (st == 2) {
         // 34 x 30 pairs for 1024 threads; the large post-passes and FP32
         // passes two slots per thread (66 x 30), small FP32 ones 66 x 14

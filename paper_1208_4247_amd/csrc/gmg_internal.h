@@ -182,7 +182,7 @@ enum PassFlags : int {
   F_PROLONG = 2,     // start value is u_in + P e_coarse (linear interpolation)
   F_NORM_IN = 4,     // emit per-workgroup partial sums of |f - A u_in|^2
   F_BLACK_FIRST = 8, // red-black order black -> red (backward sweep)
-  F_RESTRICT = 16,   // red-black: also form f_c = R (f - A u_out), the residual's
+  F_RESTRICT = 16,   // also form f_c = R (f - A u_out), the residual's
                      // full weighting onto the next coarser grid
   F_NORM_MID = 32,   // red-black, S = 2q - 1 stages: emit per-workgroup partial
                      // sums of |f - A u_q|^2, u_q the iterate after stage q
@@ -325,6 +325,9 @@ constexpr size_t kMaxPassLds = 160 * 1024;
 constexpr int rb_lds_pad(int exp_) { return (exp_ + 2) & ~1; }
 size_t rb_pass_lds_bytes(int dim, int stages, int exp_, int ey, int nt, int flags, size_t elem);
 bool rb_pass_fits(int dim, int stages, int variant, int flags, size_t elem);
+// the same of a Jacobi pass; whether it also runs with the restriction folded in
+size_t wj_pass_lds_bytes(int dim, int stages, int exp_, int ey, int flags, size_t elem);
+bool wj_pass_folds(int dim, int stages, int variant, size_t elem);
 // FNV-1a hash of the tile tables (shape of every variant index): part of the
 // autotuner's cache key, so a cached variant index never names another shape
 uint32_t tile_table_hash();

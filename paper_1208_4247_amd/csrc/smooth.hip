@@ -716,6 +716,10 @@ __global__ void __launch_bounds__(NT) k_rb_pass(PassArgs<T> arg, const PassArgs<
 // and fusions as the red-black pass (buffer loads with zero-boundary range
 // checks, pair loads, right-hand-side window, step-parity LDS buffers, the
 // coarse correction staged in LDS); a stage publishes both elements.
+// RST: two sweeps with the residual and its full weighting behind them, as in
+// the red-black pass (LDS 130 of 160 KB, 98 to 113 registers in FP64: one
+// workgroup per CU either way).  Bound by memory traffic: 255^3 with the norm
+// 128 us, against 84 us and 65 us for the restriction as a kernel of its own.
 // ------------------------------------------------------------------------
 template <typename T, int DIM, int S, int EXP, int EY, int NT, int FL>
 __global__ void __launch_bounds__(NT) k_wj_pass(PassArgs<T> arg, const PassArgs<T> *tbl,
@@ -725,7 +729,11 @@ __global__ void __launch_bounds__(NT) k_wj_pass(PassArgs<T> arg, const PassArgs<
   constexpr int PL = EXP * EY;
   constexpr int NS = (PL + NT - 1) / NT;
   constexpr bool TAIL = NS * NT > PL;
-  constexpr int HP = (S + 1) / 2;  // halo in pairs (>= S points)
+  constexpr bool RST = (FL & F_RESTRICT) != 0;
+  static_assert(!RST || S == 2, "rb_halo is the same on both sides for S = 2 alone");
+  // halo in pairs: S points, RST: two more on the high side (see the red-black
+  // pass)
+  constexpr int HP = RST ? (S + 3) / 2 : (S + 1) / 2;
   constexpr int H = 2 * HP;        // halo in rows (3D)
   constexpr int TXP = EXP - 2 * HP;
   constexpr int TY = DIM == 3 ? EY - 2 * H : 1;
@@ -737,9 +745,12 @@ __global__ void __launch_bounds__(NT) k_wj_pass(PassArgs<T> arg, const PassArgs<
   constexpr int CPL = NCX * NCY;
   constexpr int NCP = PRO ? (CPL + NT - 1) / NT : 1;
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  // [2 (step parity)][S][2 (element)][PL], then PRO: [2][CPL]
+  // [2 (step parity)][S][2 (element)][PL], RST: final plane and residual plane,
+  // each [2 (step parity)][2 (element)][PL], PRO: [2][CPL]
   T *lds = reinterpret_cast<T *>(smem_raw);
-  T *cring = lds + 4 * S * PL;
+  T *fwl = lds + 4 * S * PL;
+  T *rl = fwl + 4 * PL;
+  T *cring = lds + (4 * S + (RST ? 8 : 0)) * PL;
 
   const int m = a.m;
   int tx, ty, tzc;
@@ -806,7 +817,8 @@ __global__ void __launch_bounds__(NT) k_wj_pass(PassArgs<T> arg, const PassArgs<
       for (int e = 0; e < 2; ++e) W[s][i][e][0] = W[s][i][e][1] = W[s][i][e][2] = T(0);
   double acc = 0.0;
 
-  const int t0 = (Z0 - S) & ~1, t1 = Z1 + S;
+  const int CZ0 = Z0 >> 1, CZ1 = min(Z1 >> 1, a.mc);  // RST: coarse planes of this chunk
+  const int t0 = (Z0 - S - (RST ? 2 : 0)) & ~1, t1 = RST ? 2 * CZ1 + S + 3 : Z1 + S;
   auto load_pair = [&](const T *base, int z, T *v0, T *v1, bool mask) {
     const __amdgpu_buffer_rsrc_t rs = plane_rsrc(base, z, m, planeS);
 #pragma unroll
@@ -824,9 +836,10 @@ __global__ void __launch_bounds__(NT) k_wj_pass(PassArgs<T> arg, const PassArgs<
   } else {
     load_pair(a.u_in, t0, pu0, pu1, true);
   }
-  T fe0[S + 1][NS], fe1[S + 1][NS];  // f of plane t - j, elements 0 / 1
+  constexpr int NF = S + 1 + (RST ? 1 : 0);
+  T fe0[NF][NS], fe1[NF][NS];  // f of plane t - j, elements 0 / 1
 #pragma unroll
-  for (int j = 0; j <= S; ++j) load_pair(a.f, t0 - j, fe0[j], fe1[j], false);
+  for (int j = 0; j < NF; ++j) load_pair(a.f, t0 - j, fe0[j], fe1[j], false);
 
   const int CX0 = ((X0 - H) >> 1) - 1;
   const int CY0 = DIM == 3 ? ((Y0 - H) >> 1) - 1 : 0;
@@ -866,6 +879,19 @@ __global__ void __launch_bounds__(NT) k_wj_pass(PassArgs<T> arg, const PassArgs<
       v1 = T(0.5) * (v1 + fr);
     }
   };
+  // RST: final values of planes t-S-1 and t-S-2, this thread's coarse point
+  T fS[RST ? 2 : 1][RST ? NS : 1][2];
+#pragma unroll
+  for (int i = 0; i < (RST ? NS : 1); ++i)
+#pragma unroll
+    for (int e = 0; e < 2; ++e) fS[0][i][e] = fS[RST ? 1 : 0][i][e] = T(0);
+  constexpr int NCC = DIM == 3 ? TXP * (TY / 2) : TXP;
+  static_assert(!RST || NCC <= NT, "one thread per coarse point");
+  const int ccx = threadIdx.x % TXP, ccy = DIM == 3 ? threadIdx.x / TXP : 0;
+  const int cgx = (X0 >> 1) + ccx, cgy = DIM == 3 ? (Y0 >> 1) + ccy : 0;
+  const bool cown = RST && (int)threadIdx.x < NCC && cgx < mc && (DIM == 2 || cgy < mc);
+  const int cq = (DIM == 3 ? (H + 2 * ccy + 1) * EXP : 0) + HP + ccx;  // pair of the centre
+  T cacc = T(0);
   T cnext[NCP];
   if (PRO) {
     T cv[NCP];
@@ -904,6 +930,32 @@ __global__ void __launch_bounds__(NT) k_wj_pass(PassArgs<T> arg, const PassArgs<
     T cnn[NCP];
     if (PRO && TP == 1) load_c((t + 3) >> 1, cnn);
     const T *Lprev = lds + (1 - TP) * 2 * S * PL;
+    // ---- RST: full weighting of the residual plane t-S-2, published at step
+    // t-1 (as in the red-black pass; the centre is element 1)
+    if (RST) {
+      const int zf = t - S - 2;
+      const bool use = cown && zf >= 2 * CZ0 && zf <= 2 * CZ1;
+      T sxy = T(0);
+      if (use) {
+        const T *R0 = rl + (1 - TP) * 2 * PL, *R1 = R0 + PL;
+        auto row = [&](int q) {
+          return T(0.25) * R0[q] + T(0.5) * R1[q] + T(0.25) * R0[q + 1];
+        };
+        if (DIM == 3)
+          sxy = T(0.25) * row(cq - EXP) + T(0.5) * row(cq) + T(0.25) * row(cq + EXP);
+        else
+          sxy = row(cq);
+      }
+      if constexpr (((TP + S) & 1) != 0) {
+        if (use) cacc += T(0.5) * sxy;
+      } else {
+        const int c = zf / 2 - 1;
+        const bool cin = zf >= 2 * CZ0 && zf <= 2 * CZ1 && c >= CZ0 && c < CZ1;
+        const __amdgpu_buffer_rsrc_t rc = plane_rsrc_if(a.f_c, c, cin, cplane);
+        bstore<T>(rc, use ? (cgy * mc + cgx) * (int)sizeof(T) : kOOB, cacc + T(0.25) * sxy);
+        if (use) cacc = T(0.25) * sxy;
+      }
+    }
     // ---- stage 0: start value of plane t
     const bool tin = t >= 0 && t < m;
 #pragma unroll
@@ -987,6 +1039,42 @@ __global__ void __launch_bounds__(NT) k_wj_pass(PassArgs<T> arg, const PassArgs<
         if (xend) bstore<T>(rs, w1[i], newS[i][0]);
       }
     }
+    // ---- RST: final values of plane t-S, residual of plane t-S-1 (neighbours
+    // in the order of the separate restriction kernel)
+    if (RST) {
+      const T *F = fwl + (1 - TP) * 2 * PL;  // plane t-S-1
+      T *Fn = fwl + TP * 2 * PL, *Rn = rl + TP * 2 * PL;
+      const T inv_h2 = T(a.inv_h2);
+#pragma unroll
+      for (int i = 0; i < NS; ++i) {
+        T r[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const T side = e ? F[rgt[i]] : F[PL + lft[i]];
+          T nb = fS[0][i][1 - e] + side;
+          if (DIM == 3) {
+            nb += F[e * PL + lu[i]];
+            nb += F[e * PL + ld[i]];
+          }
+          nb += fS[RST ? 1 : 0][i][e];
+          nb += newS[i][e];
+          r[e] = (e ? fe1 : fe0)[S + (RST ? 1 : 0)][i] -
+                 (T(2 * DIM) * fS[0][i][e] - nb) * inv_h2;
+        }
+        if (!TAIL || i < NS - 1 || live[i]) {
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            Rn[e * PL + lq[i]] = r[e];
+            Fn[e * PL + lq[i]] = newS[i][e];
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          fS[RST ? 1 : 0][i][e] = fS[0][i][e];
+          fS[0][i][e] = newS[i][e];
+        }
+      }
+    }
     // ---- publish the newest plane of every stage (both elements)
     T *Lnow = lds + TP * 2 * S * PL;
 #pragma unroll
@@ -1007,7 +1095,7 @@ __global__ void __launch_bounds__(NT) k_wj_pass(PassArgs<T> arg, const PassArgs<
         pu1[i] = nu1[i];
       }
 #pragma unroll
-      for (int j = S; j >= 1; --j) {
+      for (int j = NF - 1; j >= 1; --j) {
         fe0[j][i] = fe0[j - 1][i];
         fe1[j][i] = fe1[j - 1][i];
       }
@@ -1119,6 +1207,21 @@ size_t rb_pass_lds_bytes(int dim, int stages, int exp_, int ey, int nt, int flag
   return n * elem;
 }
 
+// (see the LDS map of the pass)
+size_t wj_pass_lds_bytes(int dim, int stages, int exp_, int ey, int flags, size_t elem) {
+  size_t n = (4 * (size_t)stages + ((flags & F_RESTRICT) ? 8 : 0)) * exp_ * ey;
+  if (flags & F_PROLONG) n += 2 * (size_t)(exp_ + 1) * (dim == 3 ? ey / 2 + 1 : 1);
+  return n * elem;
+}
+
+bool wj_pass_folds(int dim, int stages, int variant, size_t elem) {
+  const PassTile t = pass_variant(dim, stages, 1, variant);
+  if (t.nt == 0 || stages != 2) return false;
+  const RbHalo h = rb_halo(stages, true);
+  return t.exp_ > h.pl + h.ph && (dim == 2 || t.ey > h.yl + h.yh) &&
+         wj_pass_lds_bytes(dim, stages, t.exp_, t.ey, F_RESTRICT | F_PROLONG, elem) <= kMaxPassLds;
+}
+
 bool rb_pass_fits(int dim, int stages, int variant, int flags, size_t elem) {
   const PassTile t = pass_variant(dim, stages, 0, variant);
   if (t.nt == 0) return false;
@@ -1173,9 +1276,13 @@ hipError_t run_rb(PassArgs<T> a, hipStream_t st, const PassArgs<T> *tbl, int nen
 
 template <typename T, int DIM, int S, int EXP, int EY, int NT, int FL>
 hipError_t run_wj(PassArgs<T> a, hipStream_t st, const PassArgs<T> *tbl, int nent) {
-  // two step-parity buffers of S planes of both elements, then the coarse ring
-  const size_t cpl = (FL & F_PROLONG) ? 2 * (size_t)(EXP + 1) * (DIM == 3 ? EY / 2 + 1 : 1) : 0;
-  const size_t lds = sizeof(T) * (4 * (size_t)S * EXP * EY + cpl);
+  constexpr RbHalo h = rb_halo(S, (FL & F_RESTRICT) != 0);
+  if constexpr ((FL & F_RESTRICT) != 0 &&
+                (S != 2 || EXP <= h.pl + h.ph || (DIM == 3 && EY <= h.yl + h.yh))) {
+    return hipErrorInvalidValue;  // this tile does not run this form
+  } else {
+  const size_t lds = wj_pass_lds_bytes(DIM, S, EXP, EY, FL, sizeof(T));
+  if (lds > kMaxPassLds) return hipErrorInvalidConfiguration;
   auto k = k_wj_pass<T, DIM, S, EXP, EY, NT, FL>;
   static int gsh = 0;
   if (gsh == 0) {
@@ -1186,10 +1293,11 @@ hipError_t run_wj(PassArgs<T> a, hipStream_t st, const PassArgs<T> *tbl, int nen
   }
   gmg_launch(k, dim3(a.nblocks, nent), dim3(NT), lds, st, a, tbl, gsh);
   return hipGetLastError();
+  }
 }
 
-// The fused-flag combinations a cycle uses (restriction: red-black only).
-#define GMG_RST_CASES_run_rb(RUN, T, D, S, E, Y, N)                                          \
+// The fused-flag combinations a cycle uses.
+#define GMG_RST_CASES(RUN, T, D, S, E, Y, N)                                          \
   case F_RESTRICT: return RUN<T, D, S, E, Y, N, F_RESTRICT>(a, st, tbl, nent);              \
   case F_RESTRICT | F_ZERO_IN: return RUN<T, D, S, E, Y, N, F_RESTRICT | F_ZERO_IN>(a, st, tbl, nent); \
   case F_RESTRICT | F_NORM_IN: return RUN<T, D, S, E, Y, N, F_RESTRICT | F_NORM_IN>(a, st, tbl, nent); \
@@ -1198,8 +1306,6 @@ hipError_t run_wj(PassArgs<T> a, hipStream_t st, const PassArgs<T> *tbl, int nen
       return RUN<T, D, S, E, Y, N, F_RESTRICT | F_ZERO_IN | F_PROLONG>(a, st, tbl, nent);      \
     else                                                                                       \
       return hipErrorInvalidValue;
-#define GMG_RST_CASES_run_wj(RUN, T, D, S, E, Y, N)
-#define GMG_RST_CASES(RUN, T, D, S, E, Y, N) GMG_RST_CASES_##RUN(RUN, T, D, S, E, Y, N)
 #define GMG_FLAG_SWITCH(RUN, T, D, S, E, Y, N)                                            \
   switch (flags) {                                                                     \
     case 0: return RUN<T, D, S, E, Y, N, 0>(a, st, tbl, nent);                                    \
