@@ -19,8 +19,9 @@
  *
  * OWNERSHIP
  *   The caller owns every device buffer (u, f, the workspace) and the stream;
- *   the library never allocates device memory (one exception: the FFT plan
- *   of the sine-transform solver, whose twiddle tables rocFFT allocates).
+ *   the library never allocates device memory (one exception: sine-transform
+ *   plans of 2D levels >= 13 and of one-node grids, whose FFT plan keeps
+ *   twiddle tables that rocFFT allocates).
  *   The library owns only the host-side plan object.  Device pointers must be hipMalloc'ed (or
  *   torch-allocated) memory of the current device, 8-byte aligned.  Arrays
  *   passed to one call must not overlap unless stated.

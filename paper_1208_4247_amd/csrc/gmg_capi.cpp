@@ -1667,6 +1667,9 @@ hipError_t tune_cross(gmg_plan *p, const T *w, const T *ec, const T *f, T *wn, T
   const int nv = pass_variant_count(p->dim, 3, 0);
   for (int v = 0; v < nv && err == hipSuccess; ++v) {
     const PassTile t = pass_variant(p->dim, 3, 0, v);
+    // two pairs per lane at 1024 threads: the FP64 build spills (59 registers;
+    // 3.5 to 7.5 times the algorithmic bytes at 1023^3), never the fastest
+    if (p->dim == 3 && sizeof(T) == 8 && t.nt == 1024 && t.exp_ * t.ey > 1024) continue;
     for (const int tzv : tune_z_chunks(p->dim, m, 3, t)) {
       if (pass_geometry(p->dim, m, 3, t, tzv).nblocks > kMaxPartials) continue;
       for (int fz = 1; fz >= 0 && err == hipSuccess; --fz) {

@@ -30,8 +30,11 @@
 //    the pass may emit per-workgroup sums of |f - A u_in|^2 (the convergence
 //    test of Algorithm 3 evaluated on the pass's input, which the pass reads
 //    anyway).
-//  * Workgroup -> tile mapping is XCD-aware: the 8 XCDs receive contiguous
-//    ranges of tiles, so halo re-reads of neighbouring tiles hit the same L2.
+//  * Workgroup -> tile mapping is XCD-aware: of each group of resident
+//    workgroups the 8 XCDs receive contiguous runs of tiles, so halo re-reads
+//    of neighbouring tiles hit the same L2 (xcd_remap).
+//  * The last pre-smoothing pass of a level can also form the residual of its
+//    result and its full weighting onto the next coarser grid.
 #include "gmg_internal.h"
 
 namespace gmg {
@@ -1232,8 +1235,7 @@ bool rb_pass_fits(int dim, int stages, int variant, int flags, size_t elem) {
 }
 
 PassGeom pass_geometry(int dim, int m, int stages, const PassTile &t, int tz, bool restrict_) {
-  // the red-black halo (rb_halo); Jacobi passes use the plain one (S points
-  // rounded up to a pair on each side)
+  // (Jacobi passes have the same halo; with the restriction, S = 2 alone)
   const RbHalo h = rb_halo(stages, restrict_);
   const int tx = 2 * (t.exp_ - h.pl - h.ph);
   PassGeom g;

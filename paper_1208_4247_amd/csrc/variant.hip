@@ -49,7 +49,8 @@ namespace gmg {
 // index gets the mean of its E[k] and E[3], one of an odd plane that of E[k] and
 // the next coarse plane's E[3].  Bound by memory traffic: interpolating in a
 // pass of its own took 60 to 69 us of a 255^3 cycle and the sweep's two launches
-// 51 us each after it; 59 us each so (127^3: 10 + 2 x 13.3 us, 2 x 11.5 us so).
+// 51 us each after it; 59 us each so (127^3: 10 + 2 x 13.3 us, 2 x 11.5 us so;
+// means over a solve, launches past its stop test included).
 // ------------------------------------------------------------------------
 struct McArgs {
   const double *src;   // old values of the planes being updated (NULL: zero)

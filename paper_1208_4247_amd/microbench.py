@@ -193,6 +193,8 @@ def cross_traffic_table(dim, m):
     for fold in (True, False):
         plan = Plan(dim, L, nu1=1, nu2=1, flags=0 if fold else capi.GMG_NO_FUSED_RESTRICT)
         for v in range(plan.tile_variants(3)):
+            if dim == 3 and v == 2:
+                continue  # 66 x 30 pairs: spills in FP64, the tuner leaves it out
             seen = set()
             for tz in tuner_tz(m):
                 try:
