@@ -40,3 +40,20 @@ def test_folded_restriction_same_bits(dim, L, variant, tz, nu1, prec):
         out.append((u.cpu().numpy(), v.cpu().numpy(), r))
     assert np.array_equal(out[0][0], out[1][0])
     assert np.array_equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("nu1", [1, 2, 4])
+def test_batch_folds_with_the_same_bits(nu1):
+    from paper_1208_4247_amd.solver import BatchPlan
+
+    problems = [(2, 8), (2, 9), (2, 6), (3, 8), (3, 5), (2, 8), (3, 4), (2, 10)]
+    fs = [torch.from_numpy(wl.rhs_uniform(d, (1 << L) - 1, seed=700 + i)).cuda()
+          for i, (d, L) in enumerate(problems)]
+    out = []
+    for flags in (0, NO_FUSED_RESTRICT):
+        plan = BatchPlan(problems, smoother="wj", nu1=nu1, nu2=1, flags=flags)
+        us = [torch.zeros_like(f) for f in fs]
+        plan.solve(us, fs, rtol=1e-30, maxit=3)
+        out.append([u.cpu().numpy() for u in us])
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
