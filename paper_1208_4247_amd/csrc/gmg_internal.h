@@ -323,6 +323,18 @@ constexpr RbHalo rb_halo(int S, bool rst) {
 constexpr size_t kMaxPassLds = 160 * 1024;
 // (elements of the pads before and after the planes: the farthest neighbour)
 constexpr int rb_lds_pad(int exp_) { return (exp_ + 2) & ~1; }
+// Where slot q of a red-black tile reads a coarse plane in the ring (row pitch
+// exp_ + 1): the lower left of the two columns (and, 3D, two rows) it
+// interpolates from.  Lanes past the tile read the first ones: their own would
+// lie up to 73 elements past the allocation (36 x 24 pairs, 256 threads).
+__host__ __device__ constexpr int rb_coarse_slot(int dim, int exp_, int ey, int q) {
+  return q >= exp_ * ey ? 0
+         : dim == 3     ? (q / exp_ + 1) / 2 * (exp_ + 1) + q % exp_
+                        : q % exp_;
+}
+// Bytes between the farthest LDS access of a red-black pass, either way, and
+// the end of its allocation: never negative
+long rb_pass_lds_slack(int dim, int stages, int variant, int flags, size_t elem);
 size_t rb_pass_lds_bytes(int dim, int stages, int exp_, int ey, int nt, int flags, size_t elem);
 bool rb_pass_fits(int dim, int stages, int variant, int flags, size_t elem);
 // the same of a Jacobi pass; whether it also runs with the restriction folded in

@@ -212,7 +212,9 @@ __global__ void __launch_bounds__(NT) k_rb_pass(PassArgs<T> arg, const PassArgs<
   // pad, [2 (step parity)][NB][PLS]; RST: final plane and residual plane, each
   // [2 (step parity)][2 (element)][PLS]; PRO: [2][CPL]; pad.  The pads keep
   // the neighbours of the first and last rows inside the allocation (their
-  // values are halo that nothing exact depends on), so no index is clamped.
+  // values are halo that nothing exact depends on), so no index of a plane is
+  // clamped; in the coarse ring, dead lanes read the first values
+  // (rb_coarse_slot).  rb_pass_lds_slack checks every tile on the host.
   // PLS is odd, and y + 1 has an index register of its own (ld): LDS accesses
   // of one lane at a distance that a paired read or write can encode are
   // otherwise merged by the compiler, and the paired forms conflict in the
@@ -288,9 +290,9 @@ __global__ void __launch_bounds__(NT) k_rb_pass(PassArgs<T> arg, const PassArgs<
     lQ[i] = par ? q - 1 : q + 1;
     pone[i] = par != 0;
     if (PRO) {
-      const int rr = DIM == 3 ? r : 0;
-      c2[i] = DIM == 3 && !(rr & 1);
-      cb[i] = (DIM == 3 ? ((rr & 1) ? (rr + 1) >> 1 : rr >> 1) * NCX : 0) + p;
+      c2[i] = DIM == 3 && !(r & 1);
+      if constexpr (NS * NT == PL) __builtin_assume(q < PL);  // no lane past the tile
+      cb[i] = rb_coarse_slot(DIM, EXP, EY, q);
     }
   }
 
@@ -805,9 +807,9 @@ __global__ void __launch_bounds__(NT) k_wj_pass(PassArgs<T> arg, const PassArgs<
     lu[i] = max(qc - EXP, 0);
     ld[i] = min(qc + EXP, PL - 1);
     if (PRO) {
-      const int rr = DIM == 3 ? r : 0;
-      c2[i] = DIM == 3 && !(rr & 1);
-      cb[i] = (DIM == 3 ? ((rr & 1) ? (rr + 1) >> 1 : rr >> 1) * NCX : 0) + p;
+      c2[i] = DIM == 3 && !(r & 1);
+      if constexpr (NS * NT == PL) __builtin_assume(q < PL);  // no lane past the tile
+      cb[i] = rb_coarse_slot(DIM, EXP, EY, q);
     }
   }
 
@@ -1215,6 +1217,26 @@ size_t wj_pass_lds_bytes(int dim, int stages, int exp_, int ey, int flags, size_
   size_t n = (4 * (size_t)stages + ((flags & F_RESTRICT) ? 8 : 0)) * exp_ * ey;
   if (flags & F_PROLONG) n += 2 * (size_t)(exp_ + 1) * (dim == 3 ? ey / 2 + 1 : 1);
   return n * elem;
+}
+
+long rb_pass_lds_slack(int dim, int stages, int variant, int flags, size_t elem) {
+  const PassTile t = pass_variant(dim, stages, 0, variant);
+  const long pad = rb_lds_pad(t.exp_);
+  const long slots = ((long)t.exp_ * t.ey + t.nt - 1) / t.nt * t.nt, pls = slots + 1;
+  const long planes = 2 * (stages + ((flags & F_NORM_IN) ? 1 : 0)) + ((flags & F_RESTRICT) ? 8 : 0);
+  long low = -t.exp_;                               // y - 1 of the first slot
+  long high = (planes - 1) * pls + slots - 1 + t.exp_;  // y + 1 of the last one, last plane
+  if (flags & F_PROLONG) {
+    // the second coarse plane: both columns and (3D) both rows of every lane
+    const long ncx = t.exp_ + 1, cpl = ncx * (dim == 3 ? (t.ey + 1) / 2 + 1 : 1);
+    for (long q = 0; q < slots; ++q) {
+      const long c = rb_coarse_slot(dim, t.exp_, t.ey, (int)q);
+      high = std::max(high, planes * pls + cpl + c + (dim == 3 ? ncx + 1 : 1));
+      low = std::min(low, planes * pls + c);
+    }
+  }
+  const long n = (long)(rb_pass_lds_bytes(dim, stages, t.exp_, t.ey, t.nt, flags, elem) / elem);
+  return std::min(pad + low, n - 1 - (pad + high)) * (long)elem;
 }
 
 bool wj_pass_folds(int dim, int stages, int variant, size_t elem) {
