@@ -19,9 +19,9 @@
  *
  * OWNERSHIP
  *   The caller owns every device buffer (u, f, the workspace) and the stream;
- *   the library never allocates device memory (one exception: sine-transform
- *   plans of 2D levels >= 13 and of one-node grids, whose FFT plan keeps
- *   twiddle tables that rocFFT allocates).
+ *   the library never allocates device memory (one exception: the twiddle
+ *   tables of a sine-transform plan, at most 164 KB of its own, or those that
+ *   rocFFT allocates).
  *   The library owns only the host-side plan object.  Device pointers must be hipMalloc'ed (or
  *   torch-allocated) memory of the current device, 8-byte aligned.  Arrays
  *   passed to one call must not overlap unless stated.
@@ -324,17 +324,21 @@ typedef struct gmg_dst gmg_dst; /* opaque, host side */
  * interior grid with zero Dirichlet data, computed as S^-1 diag(lambda)^-1 S f
  * with S the DST-I along every axis and lambda_k = sum_i (4/h^2)
  * sin^2(k_i pi h / 2) (exact up to rounding).  Two-phase like gmg_setup:
- * with workspace == NULL only *ws_bytes is written.  Otherwise workspace
- * (device memory, 256-byte aligned, at least *ws_bytes bytes, caller-owned)
- * holds the tables of the transform (at most 164 KB; the setup uploads them on
- * the stream, and gmg_dst_solve works in place in u).  dim 2 (levels <= 14) or
- * 3 (levels <= 10).  stream: a hipStream_t (NULL = default).  2D with levels
+ * with workspace == NULL only *ws_bytes is written.  Otherwise workspace is
+ * device memory, 256-byte aligned, at least *ws_bytes bytes, caller-owned, and
+ * scratch: plans used in turn may share it, and between two solves the caller
+ * may write it.  dim 2 (levels <= 14) or 3 (levels <= 10).  stream: a
+ * hipStream_t (NULL = default).  gmg_dst_solve works in place in u and needs
+ * no workspace (*ws_bytes is a nominal 256); the plan keeps the tables of the
+ * transform, at most 164 KB, in device memory that the setup allocates and
+ * uploads on the stream (released by gmg_dst_destroy).  2D with levels
  * >= 13 and one-node grids (levels 1) run rocFFT's batched FFTs instead: there
  * the workspace holds the odd extensions and the FFT coefficients of every
  * line (about 4 grids), plan creation may compile FFT kernels on first use,
  * and the plan keeps twiddle tables in device memory that rocFFT allocates
  * itself (released by gmg_dst_destroy).  Errors:
- * GMG_ERR_INVALID_ARG, GMG_ERR_WORKSPACE, GMG_ERR_HIP (FFT library failure). */
+ * GMG_ERR_INVALID_ARG, GMG_ERR_WORKSPACE, GMG_ERR_HIP (FFT library or
+ * allocation failure). */
 gmg_status gmg_dst_setup(int dim, int levels, void *workspace, size_t *ws_bytes, void *stream,
                          gmg_dst **out);
 

@@ -453,8 +453,9 @@ struct gmg_dst {
   size_t work_bytes = 0;
   rocfft_plan plan = nullptr;
   rocfft_execution_info info = nullptr;
-  // axis kernels: twiddles and eigenvalues, uploaded by the setup (the host
-  // copy stays until the plan goes)
+  // axis kernels: twiddles and eigenvalues, uploaded by the setup into memory
+  // of the plan's own (the workspace is scratch: its contents need not outlive
+  // a solve; the host copy stays until the plan goes)
   bool axis = false;
   double2 *tw = nullptr;
   double *eig = nullptr;
@@ -531,25 +532,24 @@ hipError_t dst_pass(gmg_dst *p, double *out, int eig, double scale) {
   return hipGetLastError();
 }
 
-// Set-up for the axis kernels: the tables in the workspace.
+// Set-up for the axis kernels: they need no workspace (the nominal size keeps
+// the two-phase call alike for every size) and keep their tables, at most
+// 164 KB, in an allocation of the plan's own.
 gmg_status axis_setup(int dim, int m, void *workspace, size_t *ws_bytes, hipStream_t stream,
                       gmg_dst **out) {
   const int N = 2 * (m + 1);
   const size_t ntw = 2 * (size_t)N, nd = ntw + (size_t)m + 1;
-  const size_t total = up(nd * sizeof(double));
   if (!workspace) {
-    *ws_bytes = total;
+    *ws_bytes = kAlignDst;
     return GMG_OK;
   }
   if (!out) return GMG_ERR_INVALID_ARG;
-  if (*ws_bytes < total || ((uintptr_t)workspace) % kAlignDst) return GMG_ERR_WORKSPACE;
+  if (*ws_bytes < kAlignDst || ((uintptr_t)workspace) % kAlignDst) return GMG_ERR_WORKSPACE;
   gmg_dst *p = new gmg_dst();
   p->axis = true;
   p->dim = dim;
   p->m = m;
   p->stream = stream;
-  p->tw = (double2 *)workspace;
-  p->eig = (double *)workspace + ntw;
   p->host.resize(nd);
   const long double pi = 3.141592653589793238462643383279502884L;
   for (int k = 0; k < N; ++k) {
@@ -561,8 +561,14 @@ gmg_status axis_setup(int dim, int m, void *workspace, size_t *ws_bytes, hipStre
     const long double sv = sinl(pi * k / (2 * (m + 1)));
     p->host[ntw + k] = (double)(4 * n2 * sv * sv);
   }
-  if (hipMemcpyAsync(workspace, p->host.data(), nd * sizeof(double), hipMemcpyHostToDevice,
-                     stream) != hipSuccess) {
+  if (hipMalloc((void **)&p->tw, nd * sizeof(double)) != hipSuccess) {
+    delete p;
+    return GMG_ERR_HIP;
+  }
+  p->eig = (double *)p->tw + ntw;
+  if (hipMemcpyAsync(p->tw, p->host.data(), nd * sizeof(double), hipMemcpyHostToDevice, stream) !=
+      hipSuccess) {
+    (void)hipFree(p->tw);
     delete p;
     return GMG_ERR_HIP;
   }
@@ -686,6 +692,7 @@ gmg_status gmg_dst_destroy(gmg_dst *p) {
   if (!p) return GMG_ERR_INVALID_ARG;
   if (p->info) rocfft_execution_info_destroy(p->info);
   if (p->plan) rocfft_plan_destroy(p->plan);
+  if (p->tw) (void)hipFree(p->tw);  // waits for solves still running
   delete p;
   return GMG_OK;
 }
