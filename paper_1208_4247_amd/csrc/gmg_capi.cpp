@@ -324,10 +324,10 @@ int stages_of(const gmg_plan *p, int sweeps) {
 template <typename T>
 hipError_t one_pass_st(gmg_plan *p, int level, int role, int st, int flags, const T *src,
                        const T *ec, const T *f, T *dst, double *partials, const int *active,
-                       int cls, T *fc = nullptr) {
+                       int cls, T *fc = nullptr, const PassChoice *choice = nullptr) {
   const int dim = p->dim, m = p->m[level];
   const bool wj = p->cfg.smoother == GMG_SMOOTH_WJ;
-  const PassChoice &c = p->ch[level][role];
+  const PassChoice &c = choice ? *choice : p->ch[level][role];
   const int v = c.var[st];
   const PassTile t = pass_variant(dim, st, wj ? 1 : 0, v);
   const PassGeom g = pass_geometry(dim, m, st, t, c.tz[st], (flags & F_RESTRICT) != 0);
@@ -528,14 +528,25 @@ bool can_fuse_cross(const gmg_plan *p, size_t elem) {
   return rb_pass_fits(p->dim, 3, c.var[3], (p->carry ? F_NORM_IN : F_PROLONG) | F_RESTRICT, elem);
 }
 
-// The tile of the three-stage pass for the form it runs next: a tile made for
-// the folded form (odd row count) cannot run the plain one, which then takes
-// the first tile of the table.  Returns the launch's workgroup count.
-int three_stage_tile(gmg_plan *p, int plain_flags, bool folded, size_t elem) {
-  PassChoice &c = p->ch[0][2];
-  if (!folded && !rb_pass_fits(p->dim, 3, c.var[3], plain_flags, elem)) c.var[3] = 0;
-  return pass_geometry(p->dim, p->m[0], 3, pass_variant(p->dim, 3, 0, c.var[3]), c.tz[3], folded)
-      .nblocks;
+PassChoice choice_for(const gmg_config &cfg, int dim, int m, int role, int smax_cap);
+
+// The plan's choice for the three-stage pass in the form it runs next.  A tile
+// made for the folded form (odd row count) cannot run the plain one: that takes
+// the default plain tile and its z-chunk (the plan's choice stays as it is).
+PassChoice three_stage_choice(const gmg_plan *p, int plain_flags, bool folded, size_t elem,
+                              int *nblocks) {
+  PassChoice c = p->ch[0][2];
+  if (!folded && !rb_pass_fits(p->dim, 3, c.var[3], plain_flags, elem)) {
+    gmg_config plain = p->cfg;
+    plain.flags |= GMG_NO_FUSED_RESTRICT;
+    const PassChoice d = choice_for(plain, p->dim, p->m[0], 2, p->smax_cap);
+    c.var[3] = d.var[3];
+    c.tz[3] = d.tz[3];
+  }
+  *nblocks = pass_geometry(p->dim, p->m[0], 3, pass_variant(p->dim, 3, 0, c.var[3]), c.tz[3],
+                           folded)
+                 .nblocks;
+  return c;
 }
 
 // partials != NULL (FP64 solves): the pass emits the norm of u_k's residual.
@@ -546,11 +557,11 @@ hipError_t cross_pass(gmg_plan *p, const T *w, const T *ec, const T *f, T *w_nex
                       double *partials, const int *active, T *fc, bool *fused, int *nparts) {
   const bool fz = can_fuse_cross(p, sizeof(T));
   *fused = fz;
-  *nparts = three_stage_tile(p, F_PROLONG, fz, sizeof(T));
+  const PassChoice c = three_stage_choice(p, F_PROLONG, fz, sizeof(T), nparts);
   const int flags =
       F_PROLONG | F_BLACK_FIRST | (partials ? F_NORM_MID : 0) | (fz ? F_RESTRICT : 0);
   return one_pass_st<T>(p, 0, 2, 3, flags, w, ec, f, w_next, partials, active, PC_CROSS0,
-                        fz ? fc : nullptr);
+                        fz ? fc : nullptr, &c);
 }
 
 // The level-0 pre-smoothing of a cycle that starts from the previous cycle's
@@ -571,7 +582,8 @@ hipError_t carry_pre(gmg_plan *p, const T *u, const T *f, T *w, T *tmp, double *
                      const int *active, T *fc, bool *fused, int *nparts) {
   const int left = p->cfg.nu1 - 2;  // sweeps after the three stages
   const bool fz = left == 0 && can_fuse_cross(p, sizeof(T));
-  const int nb = three_stage_tile(p, partials ? F_NORM_IN : 0, fz, sizeof(T));
+  int nb = 0;
+  const PassChoice c = three_stage_choice(p, partials ? F_NORM_IN : 0, fz, sizeof(T), &nb);
   if (nparts) *nparts = nb;
   *fused = fz;
   const int flags = F_BLACK_FIRST | (partials ? F_NORM_IN : 0) | (fz ? F_RESTRICT : 0);
@@ -579,7 +591,7 @@ hipError_t carry_pre(gmg_plan *p, const T *u, const T *f, T *w, T *tmp, double *
   const int smax = p->ch[0][0].smax;
   T *out = left > 0 && ((left + smax - 1) / smax) % 2 == 1 ? tmp : w;
   hipError_t e = one_pass_st<T>(p, 0, 2, 3, flags, u, nullptr, f, out, partials, active, PC_PRE0,
-                                fz ? fc : nullptr);
+                                fz ? fc : nullptr, &c);
   if (e != hipSuccess || left == 0) return e;
   return smooth_chain<T>(p, 0, left, false, out, nullptr, f, w, tmp, nullptr, active, PC_PRE0,
                          nullptr, fc, fused);
@@ -1203,6 +1215,8 @@ PassChoice choice_for(const gmg_config &cfg, int dim, int m, int role, int smax_
   c.smax = smax_cap;
   if (wj)
     c.fuse = m >= 255;
+  else if (role == 2 && cfg.nu1 > 2)
+    c.fuse = 0;  // (sweeps follow the three stages: nothing to fold)
   else if (dim == 3)
     c.fuse = role == 2 ? m >= 255 : (cfg.nu1 == 1 ? m >= 255 : fp32 && m >= 511);
   else
@@ -1652,9 +1666,10 @@ hipError_t tune_cross(gmg_plan *p, const T *w, const T *ec, const T *f, T *wn, T
     bool fused = false;
     int nparts = 0;
     if (alone) {
-      three_stage_tile(p, parts ? F_NORM_IN : 0, false, sizeof(T));
+      int nb = 0;
+      const PassChoice c = three_stage_choice(p, parts ? F_NORM_IN : 0, false, sizeof(T), &nb);
       return one_pass_st<T>(p, 0, 2, 3, F_BLACK_FIRST | (parts ? F_NORM_IN : 0), w, nullptr, f,
-                            wn, parts, nullptr, PC_MISC);
+                            wn, parts, nullptr, PC_MISC, nullptr, &c);
     }
     hipError_t e2 =
         ec ? cross_pass<T>(p, w, ec, f, wn, parts, nullptr, fc, &fused, &nparts)
