@@ -239,7 +239,10 @@ int gmg_tile_variant_count(int dim, gmg_smoother smoother, int stages);
 /* Override the tile shape (index < gmg_tile_variant_count) and the z-chunk
  * (output planes per workgroup; 0 = automatic) used on level `level` of
  * problem 0 for passes with `stages` stages (red-black 3: the three-stage
- * pass between cycles, level 0 only).  Results do not depend on the choice (tests check
+ * pass between cycles, level 0 only).  A tile that can run the pass with the
+ * restriction folded in does so, unless the plan has GMG_NO_FUSED_RESTRICT;
+ * a three-stage tile that runs neither form of the plan's pass is refused
+ * (GMG_ERR_INVALID_ARG).  Results do not depend on the choice (tests check
  * this bitwise); only speed does.  Host only. */
 gmg_status gmg_plan_set_tile(gmg_plan *p, int level, int stages, int variant, int tz);
 

@@ -2775,6 +2775,7 @@ gmg_status gmg_plan_set_tile(gmg_plan *p, int level, int stages, int variant, in
     PassChoice &c = p->ch[0][2];
     c.var[3] = variant;
     c.tz[3] = tzv;
+    c.fuse = fold ? 1 : 0;  // the form the tile was checked for
     return GMG_OK;
   }
   const int sweeps = wj ? stages : stages / 2;
@@ -2784,6 +2785,7 @@ gmg_status gmg_plan_set_tile(gmg_plan *p, int level, int stages, int variant, in
     c.var[stages] = variant;
     c.tz[stages] = tzv;
     c.smax = sweeps;
+    if (role == 0) c.fuse = 1;  // folds the restriction in where the tile can
   }
   return GMG_OK;
 }
