@@ -211,7 +211,7 @@ size_t small_lds_bytes(int dim, int nsweeps, size_t elem) {
 }
 
 bool small_level_ok(int dim, int m, int nsweeps, size_t elem) {
-  if (nsweeps < 1 || nsweeps > 3) return false;
+  if (nsweeps < 1 || nsweeps > (dim == 3 ? 2 : 3)) return false;  // the kernels there are
   if (dim == 3 ? m > 63 : m > 511) return false;
   return small_lds_bytes(dim, nsweeps, elem) <= 120 * 1024;
 }
