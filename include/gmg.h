@@ -260,7 +260,8 @@ gmg_status gmg_plan_set_tile_order(gmg_plan *p, int level, int stages, int strip
  * its stage count, tile index and z-chunk (resolved, > 0).  Role 2: the
  * three-stage pass of level 0 between two cycles (plans that run it).  Host only; any output
  * pointer may be NULL.  GMG_ERR_INVALID_ARG for a bad level/role, a batch
- * plan, or a role without sweeps. */
+ * plan, a role without sweeps, or a stage count without tiles (a
+ * GMG_SMOOTH_MCGS plan of one sweep; such plans run no fused pass). */
 gmg_status gmg_plan_get_tile(const gmg_plan *p, int level, int role, int *stages, int *variant,
                              int *tz);
 

@@ -2820,6 +2820,7 @@ gmg_status gmg_plan_get_tile(const gmg_plan *p, int level, int role, int *stages
   }
   const PassChoice &c = p->ch[level][role];
   const PassTile t = pass_variant(p->dim, st, wj, c.var[st]);
+  if (t.nt == 0) return GMG_ERR_INVALID_ARG;  // no fused pass of that many stages (MCGS)
   if (stages) *stages = st;
   if (variant) *variant = c.var[st];
   if (tz) *tz = c.tz[st] > 0 ? std::min(c.tz[st], p->m[level])
