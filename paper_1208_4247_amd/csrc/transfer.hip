@@ -662,7 +662,9 @@ template <typename T>
 hipError_t launch_restrict(int dim, RestrictArgs<T> a, hipStream_t s, const RestrictArgs<T> *tbl,
                            int nent) {
   const int mc = a.mc;
-  if (!a.u) {  // zero iterate: the right-hand side itself (no stop test, no table)
+  if (!a.u) {  // zero iterate: the right-hand side itself
+    // (full multigrid's alone: that kernel knows no table and no stop test)
+    if (tbl || nent != 1 || a.fin_partials || a.fin_state) return hipErrorInvalidValue;
     // chunks short enough that a few thousand wavefronts hide the latency
     const int chunk = dim == 3 ? (mc >= 128 ? 8 : 2) : (mc >= 2047 ? 8 : mc >= 1023 ? 4 : 2);
     const int parts = (mc + chunk - 1) / chunk;
