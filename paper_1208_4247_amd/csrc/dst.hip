@@ -417,12 +417,14 @@ hipError_t run_axis(DstAxisArgs a, int outers, hipStream_t s) {
   return hipGetLastError();
 }
 
-// mode 0: rows, 1: strided, 2: strided with the eigenvalue division
+// mode 0: rows, 1: strided (the middle axis, 3D: N <= 2048), 2: strided with the
+// eigenvalue division
 template <int LOGN>
 hipError_t run_axis_mode(int mode, const DstAxisArgs &a, int outers, hipStream_t s) {
-  return mode == 0   ? run_axis<LOGN, true, false>(a, 1, s)
-         : mode == 1 ? run_axis<LOGN, false, false>(a, outers, s)
-                     : run_axis<LOGN, false, true>(a, outers, s);
+  if (mode == 0) return run_axis<LOGN, true, false>(a, 1, s);
+  if (mode == 2) return run_axis<LOGN, false, true>(a, outers, s);
+  if constexpr (LOGN <= 11) return run_axis<LOGN, false, false>(a, outers, s);
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_axis(int logn, int mode, const DstAxisArgs &a, int outers, hipStream_t s) {
