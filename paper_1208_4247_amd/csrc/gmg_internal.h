@@ -323,18 +323,29 @@ constexpr RbHalo rb_halo(int S, bool rst) {
 constexpr size_t kMaxPassLds = 160 * 1024;
 // (elements of the pads before and after the planes: the farthest neighbour)
 constexpr int rb_lds_pad(int exp_) { return (exp_ + 2) & ~1; }
-// Where slot q of a red-black tile reads a coarse plane in the ring (row pitch
+// Where slot q of a tile reads a coarse plane in the ring (row pitch
 // exp_ + 1): the lower left of the two columns (and, 3D, two rows) it
-// interpolates from.  Lanes past the tile read the first ones: their own would
-// lie up to 73 elements past the allocation (36 x 24 pairs, 256 threads).
-__host__ __device__ constexpr int rb_coarse_slot(int dim, int exp_, int ey, int q) {
-  return q >= exp_ * ey ? 0
-         : dim == 3     ? (q / exp_ + 1) / 2 * (exp_ + 1) + q % exp_
-                        : q % exp_;
+// interpolates from.
+__host__ __device__ constexpr int rb_coarse_slot(int dim, int exp_, int q) {
+  return dim == 3 ? ((q / exp_ + 1) >> 1) * (exp_ + 1) + q % exp_ : q % exp_;
 }
-// Bytes between the farthest LDS access of a red-black pass, either way, and
-// the end of its allocation: never negative
+// Elements past the last pad that lanes beyond the tile (whose values nothing
+// uses) read so: up to 73 (36 x 24 pairs on 256 threads), 0 for most tiles.
+// Room for them costs nothing; clamping the index took 0.3 us of a 63^3 V-cycle.
+constexpr int rb_ring_over(int dim, int exp_, int ey, int nt) {
+  const int slots = (exp_ * ey + nt - 1) / nt * nt, ncx = exp_ + 1;
+  int far = 0;
+  for (int q = 0; q < slots; ++q) {
+    const int c = rb_coarse_slot(dim, exp_, q) + (dim == 3 ? ncx + 1 : 1);
+    far = c > far ? c : far;
+  }
+  const int end = ncx * (dim == 3 ? (ey + 1) / 2 + 1 : 1) + rb_lds_pad(exp_);
+  return far < end ? 0 : far + 1 - end;
+}
+// Bytes between the farthest LDS access of a pass, either way, and the end of its
+// allocation: never negative
 long rb_pass_lds_slack(int dim, int stages, int variant, int flags, size_t elem);
+long wj_pass_lds_slack(int dim, int stages, int variant, int flags, size_t elem);
 size_t rb_pass_lds_bytes(int dim, int stages, int exp_, int ey, int nt, int flags, size_t elem);
 bool rb_pass_fits(int dim, int stages, int variant, int flags, size_t elem);
 // the same of a Jacobi pass; whether it also runs with the restriction folded in

@@ -212,9 +212,9 @@ __global__ void __launch_bounds__(NT) k_rb_pass(PassArgs<T> arg, const PassArgs<
   // pad, [2 (step parity)][NB][PLS]; RST: final plane and residual plane, each
   // [2 (step parity)][2 (element)][PLS]; PRO: [2][CPL]; pad.  The pads keep
   // the neighbours of the first and last rows inside the allocation (their
-  // values are halo that nothing exact depends on), so no index of a plane is
-  // clamped; in the coarse ring, dead lanes read the first values
-  // (rb_coarse_slot).  rb_pass_lds_slack checks every tile on the host.
+  // values are halo that nothing exact depends on), and the last one what lanes
+  // past the tile read of the ring (rb_ring_over), so no index is clamped;
+  // rb_pass_lds_slack checks every tile on the host.
   // PLS is odd, and y + 1 has an index register of its own (ld): LDS accesses
   // of one lane at a distance that a paired read or write can encode are
   // otherwise merged by the compiler, and the paired forms conflict in the
@@ -291,8 +291,7 @@ __global__ void __launch_bounds__(NT) k_rb_pass(PassArgs<T> arg, const PassArgs<
     pone[i] = par != 0;
     if (PRO) {
       c2[i] = DIM == 3 && !(r & 1);
-      if constexpr (NS * NT == PL) __builtin_assume(q < PL);  // no lane past the tile
-      cb[i] = rb_coarse_slot(DIM, EXP, EY, q);
+      cb[i] = rb_coarse_slot(DIM, EXP, q);
     }
   }
 
@@ -808,8 +807,7 @@ __global__ void __launch_bounds__(NT) k_wj_pass(PassArgs<T> arg, const PassArgs<
     ld[i] = min(qc + EXP, PL - 1);
     if (PRO) {
       c2[i] = DIM == 3 && !(r & 1);
-      if constexpr (NS * NT == PL) __builtin_assume(q < PL);  // no lane past the tile
-      cb[i] = rb_coarse_slot(DIM, EXP, EY, q);
+      cb[i] = rb_coarse_slot(DIM, EXP, qc);
     }
   }
 
@@ -1208,7 +1206,8 @@ size_t rb_pass_lds_bytes(int dim, int stages, int exp_, int ey, int nt, int flag
   const size_t pl = ((size_t)exp_ * ey + nt - 1) / nt * nt + 1;
   size_t n = 2 * pl * (size_t)(stages + ((flags & F_NORM_IN) ? 1 : 0)) + 2 * rb_lds_pad(exp_);
   if (flags & F_RESTRICT) n += 8 * pl;
-  if (flags & F_PROLONG) n += 2 * (size_t)(exp_ + 1) * (dim == 3 ? (ey + 1) / 2 + 1 : 1);
+  if (flags & F_PROLONG)
+    n += 2 * (size_t)(exp_ + 1) * (dim == 3 ? (ey + 1) / 2 + 1 : 1) + rb_ring_over(dim, exp_, ey, nt);
   return n * elem;
 }
 
@@ -1230,13 +1229,30 @@ long rb_pass_lds_slack(int dim, int stages, int variant, int flags, size_t elem)
     // the second coarse plane: both columns and (3D) both rows of every lane
     const long ncx = t.exp_ + 1, cpl = ncx * (dim == 3 ? (t.ey + 1) / 2 + 1 : 1);
     for (long q = 0; q < slots; ++q) {
-      const long c = rb_coarse_slot(dim, t.exp_, t.ey, (int)q);
+      const long c = rb_coarse_slot(dim, t.exp_, (int)q);
       high = std::max(high, planes * pls + cpl + c + (dim == 3 ? ncx + 1 : 1));
       low = std::min(low, planes * pls + c);
     }
   }
   const long n = (long)(rb_pass_lds_bytes(dim, stages, t.exp_, t.ey, t.nt, flags, elem) / elem);
   return std::min(pad + low, n - 1 - (pad + high)) * (long)elem;
+}
+
+// Jacobi: lanes past the tile take its last slot, and no index leaves the planes
+long wj_pass_lds_slack(int dim, int stages, int variant, int flags, size_t elem) {
+  const PassTile t = pass_variant(dim, stages, 1, variant);
+  const long pl = (long)t.exp_ * t.ey, planes = 4 * stages + ((flags & F_RESTRICT) ? 8 : 0);
+  long high = planes * pl - 1;
+  if (flags & F_PROLONG) {
+    const long ncx = t.exp_ + 1, cpl = ncx * (dim == 3 ? t.ey / 2 + 1 : 1);
+    for (long q = 0; q < pl; ++q) {
+      const bool two_rows = dim == 3 && (q / t.exp_) % 2 == 0;
+      high = std::max(high, planes * pl + cpl + rb_coarse_slot(dim, t.exp_, (int)q) +
+                                (two_rows ? ncx + 1 : 1));
+    }
+  }
+  const long n = (long)(wj_pass_lds_bytes(dim, stages, t.exp_, t.ey, flags, elem) / elem);
+  return (n - 1 - high) * (long)elem;
 }
 
 bool wj_pass_folds(int dim, int stages, int variant, size_t elem) {
