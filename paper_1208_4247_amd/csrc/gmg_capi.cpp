@@ -572,8 +572,9 @@ hipError_t cross_pass(gmg_plan *p, const T *w, const T *ec, const T *f, T *w_nex
 // instead of a four-stage one.  A shorter halo, and enough LDS and registers
 // left for the folded restriction: the four-stage pass spills with it, so the
 // restriction was a kernel of its own, another read of w and f.  HBM bound,
-// 25 B per point instead of 24 + 17.  511^3 FP64: 848-893 us against 723 +
-// 599 us (V(2,2) solve 30.1 -> 24.8 ms); 255^3: 127 against 93 + 60 us.
+// 25 B per point instead of 24 + 17.  511^3 FP64: 830-855 us (by machine)
+// against 665-700 + 590 us (V(2,2) solve 30.1 -> 24.3 ms); 255^3: 122 against
+// 90 + 60 us.
 // nu1 > 2: the remaining sweeps follow as a chain.  Same iterates, same norm
 // of u's residual (partials).  A batch keeps the four-stage pass: sharing its
 // launches among problems the two forms came out equal (35.9 ms both).
@@ -1188,9 +1189,14 @@ int auto_tz(int dim, int m, int st, const PassTile &t) {
   return std::max(tzv, std::min(m, 8));
 }
 
-// Default pass choice for a level and role: what the tuner picks on MI355X,
-// which depends on the size in a regular way (both sides of each line below as
-// measured, FP64 unless stated; the step is the pass and what follows it).
+// Default pass choice for a level and role: what the tuner picks on MI355X or a
+// choice within a few percent of it (both sides of each line below as measured,
+// FP64 unless stated; the step is the pass and what follows it).  Where the
+// tuner's pick changes from run to run the rule has one of the two: 511^3
+// three-stage pass 37 x 25 pairs 830 us, 33 x 31 843-853; 511^3 four-stage
+// pre-pass 36 x 24 in chunks of 256 680-691 us, 36 x 28 in chunks of 86 665-679
+// (a solve runs it once); 127^3 four-stage post-pass 36 x 24 22.8 us, 36 x 28
+// 22.9.
 //  * Two sweeps per pass wherever there are two: one pass of four stages
 //    against two of two stages is 17.4 against 2 x 10.7 us at 63^3, 7.0
 //    against 2 x 5.4 us at 255^2, and half the traffic on large grids.
@@ -1201,7 +1207,7 @@ int auto_tz(int dim, int m, int st, const PassTile &t) {
 //    chunks of 4 with a large tile, 24 us in chunks of 8 with the 36 x 24 one.
 //  * The restriction folded into the last pre-smoothing pass: where its halo
 //    costs less than reading w and f again, which is large grids (255^3
-//    three-stage pass 126 against 90 + 60 us; at 127^3 the tuner keeps the
+//    three-stage pass 122 against 90 + 60 us; at 127^3 the tuner keeps the
 //    two, 35 us together); not into the four-stage FP64 pass, which has no
 //    registers left for it (the tuner never folds it, 1266 us at 511^3).
 //    Jacobi's two-sweep pass: from side 255 up (V(2,2) cycle 511^3 1866 against
@@ -1682,7 +1688,7 @@ hipError_t tune_cross(gmg_plan *p, const T *w, const T *ec, const T *f, T *wn, T
   const int nv = pass_variant_count(p->dim, 3, 0);
   for (int v = 0; v < nv && err == hipSuccess; ++v) {
     const PassTile t = pass_variant(p->dim, 3, 0, v);
-    // two pairs per lane at 1024 threads: the FP64 build spills (59 registers;
+    // two pairs per lane at 1024 threads: the FP64 build spills (65 registers;
     // 3.5 to 7.5 times the algorithmic bytes at 1023^3), never the fastest
     if (p->dim == 3 && sizeof(T) == 8 && t.nt == 1024 && t.exp_ * t.ey > 1024) continue;
     for (const int tzv : tune_z_chunks(p->dim, m, 3, t)) {

@@ -100,47 +100,6 @@ __device__ __forceinline__ void block_sum_store(double acc, GMG_GLOBAL double *o
 }
 
 // ------------------------------------------------------------------------
-// Per-slot geometry shared by the passes.  A slot is a pair of adjacent x
-// columns (xb, xb+1), xb even, in row y of the extended tile.
-// ------------------------------------------------------------------------
-struct SlotGeo {
-  int off;       // y*m + xb (3D) / xb (2D): offset inside a plane
-  int q;         // slot index inside the tile (LDS position)
-  int par;       // (y + DIM) & 1: element e has colour (e + par + z) & 1
-  int ok;        // bit0 / bit1: element 0 / 1 inside the domain (x and y); bit2 live
-  int outp;      // slot belongs to the output tile
-  int y;         // row (3D) or 0
-  int xb;
-};
-
-template <int DIM, int S_HALO, int EXP, int EY, int NT, int NS>
-__device__ __forceinline__ void slot_setup(SlotGeo (&g)[NS], int X0, int Y0, int m) {
-  constexpr int PL = EXP * EY;
-  constexpr int HP = (S_HALO + 1) / 2;
-  constexpr int H = 2 * HP;
-  constexpr int TXP = EXP - 2 * HP;
-  constexpr int TY = DIM == 3 ? EY - 2 * H : 1;
-#pragma unroll
-  for (int i = 0; i < NS; ++i) {
-    const int q = threadIdx.x + NT * i;
-    const bool live = q < PL;
-    const int p = q % EXP, r = q / EXP;
-    const int xb = X0 - H + 2 * p;
-    const int y = DIM == 3 ? Y0 - H + r : 0;
-    const bool yin = DIM == 2 || (y >= 0 && y < m);
-    g[i].q = live ? q : PL - 1;
-    g[i].xb = xb;
-    g[i].y = y;
-    g[i].off = (DIM == 3 ? y * m : 0) + xb;
-    g[i].par = (y + DIM) & 1;
-    g[i].ok = ((live && yin && xb >= 0 && xb < m) ? 1 : 0) |
-              ((live && yin && xb + 1 >= 0 && xb + 1 < m) ? 2 : 0) | (live ? 4 : 0);
-    g[i].outp = live && yin && p >= HP && p < HP + TXP &&
-                (DIM == 2 || (r >= H && r < H + TY)) && xb < m;
-  }
-}
-
-// ------------------------------------------------------------------------
 // Red-black Gauss-Seidel pass: S half-sweeps, colour of stage s is
 // (C1 + s - 1) mod 2 with C1 = 0 (red first) or 1 (black first).
 //
@@ -1130,9 +1089,11 @@ __global__ void __launch_bounds__(NT) k_wj_pass(PassArgs<T> arg, const PassArgs<
 // (Tiles with an even row count run the plain form, odd ones the form with
 // the restriction folded in: its halo is one row taller on the high side.
 // The last two have a 64 x 16 output, which divides the sides 2^k - 1 with no
-// remainder to speak of: 255^3 in chunks of 64 is one workgroup per CU.  511^3
-// pre-smoothing of a repeated cycle, folded: 37 x 25 takes 875 us, 34 x 29
-// takes 916 us.)
+// remainder to speak of: 255^3 in chunks of 64 is one workgroup per CU.
+// Pre-smoothing of a repeated cycle, folded: 511^3 in chunks of 256, 37 x 25
+// takes 830 us, 33 x 31 843-853, 34 x 29 837-883, 36 x 27 1150; 255^3 in
+// chunks of 64, 37 x 25 121, 33 x 31 123, 34 x 29 207 us.  The first and the
+// second are a few percent apart at 511^3, so the tuner takes either.)
 #define GMG_RB3_S3(X) \
   X(3, 3, 34, 30, 1024) X(3, 3, 36, 28, 1024) X(3, 3, 66, 30, 1024) X(3, 3, 34, 30, 512) \
   X(3, 3, 66, 14, 512) X(3, 3, 34, 29, 1024) X(3, 3, 36, 27, 1024) X(3, 3, 33, 31, 1024) \
