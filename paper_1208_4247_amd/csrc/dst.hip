@@ -42,6 +42,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <new>
 #include <vector>
 
 #include "../../include/gmg.h"
@@ -547,12 +548,18 @@ gmg_status axis_setup(int dim, int m, void *workspace, size_t *ws_bytes, hipStre
   }
   if (!out) return GMG_ERR_INVALID_ARG;
   if (*ws_bytes < kAlignDst || ((uintptr_t)workspace) % kAlignDst) return GMG_ERR_WORKSPACE;
-  gmg_dst *p = new gmg_dst();
+  gmg_dst *p = new (std::nothrow) gmg_dst();
+  if (!p) return GMG_ERR_HIP;
+  try {  // nothing throws across the C entry
+    p->host.resize(nd);
+  } catch (const std::bad_alloc &) {
+    delete p;
+    return GMG_ERR_HIP;
+  }
   p->axis = true;
   p->dim = dim;
   p->m = m;
   p->stream = stream;
-  p->host.resize(nd);
   const long double pi = 3.141592653589793238462643383279502884L;
   for (int k = 0; k < N; ++k) {
     p->host[2 * k] = (double)cosl(2 * pi * k / N);
